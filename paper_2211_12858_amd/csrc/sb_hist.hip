@@ -556,16 +556,36 @@ __device__ inline void run_segment_rot(const HistArgs& a, lds_u64* lds, int64_t*
   }
 }
 
+// Sum over the R = 16 / FT copies of a thin slice's cell, which the lanes of
+// a row of 16 hold in slots feature + FT * copy: rotations inside the row
+// (DPP, in registers) leave every lane with its feature's sum.
+template <int CTRL>
+__device__ inline int64_t dpp_row_ror(int64_t x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, 0xf, 0xf, false);
+  return ((int64_t)hi << 32) | (uint32_t)lo;
+}
+template <int FT>
+__device__ inline int64_t sum_copies(int64_t x) {
+  if constexpr (FT <= 8) x += dpp_row_ror<0x128>(x);
+  if constexpr (FT <= 4) x += dpp_row_ror<0x124>(x);
+  if constexpr (FT <= 2) x += dpp_row_ror<0x122>(x);
+  if constexpr (FT <= 1) x += dpp_row_ror<0x121>(x);
+  return x;
+}
+
 // One workgroup's share of a level: the slice's cells in [bin][pair][slot]
 // order, thread t owning the 64-bit cells t + ROT_THREADS * i, i < ROT_CPT.
-// At the end of a node's part the totals go out through LDS, one pair at a
-// time, as partials laid out [pair][feature][bin] (16-byte channel pairs).
+// At the end of a node's part the totals go out through LDS, all pairs at
+// once, as int32 partials laid out [pair][feature][bin].  (One pair at a time
+// through 16-byte int64 pairs, two barriers each, a node's end cost 11 us: 29
+// of the 92 us of a 2M-row level of 16 built nodes, and 124 of the 268 us of
+// a level of 64 built nodes x 200 features x 11 channels.)
 // Slice s of FT features (16, or a thin slice's f_thin), row group q of
 // qn: the rows of virtual positions [q T / qn, (q+1) T / qn).
 template <int C, int FT>
 __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds64, int s, int grp, int q, int qn) {
   constexpr int P = (C + 1) / 2;
-  constexpr int R = ROT_F / FT;  // copies of each cell in the slice
   const int64_t T = a.pre[a.n_build];
   const int64_t v0 = (int64_t)q * T / qn;
   const int64_t v1 = (int64_t)(q + 1) * T / qn;
@@ -591,7 +611,11 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
   for (int i = 0; i < ROT_CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
   __syncthreads();
 
-  longlong2* stage = reinterpret_cast<longlong2*>(lds64);  // [slot][B + 1] channel pairs
+  // staging of a node's partials: int32 channel pairs [pair][feature][bin] in
+  // rows of ld, ld mod 32 == 2, and pairs ps apart, so that the 16 features x
+  // 4 (bin, pair) rows that a wave writes at once spread over the banks
+  int2* stage = reinterpret_cast<int2*>(lds64);
+  const int ld = rot_stage_ld(B), ps = ROT_F * ld + 1;
   int64_t v = v0;
   while (v < v1) {
     const int32_t j = node_of(a, p);
@@ -613,41 +637,46 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
     const int64_t slot = ((int64_t)s * a.slots + q + p) * a.cells;  // channel cells
     int2* dst = reinterpret_cast<int2*>(a.part32 + slot);
     longlong2* dov = reinterpret_cast<longlong2*>(a.ovf + slot);
-    // this channel group's pairs are pairs 3 grp .. 3 grp + P - 1 of the
-    // slot; pairs past the last (a short final group) are not written
-#pragma unroll 1
-    for (int pr = 0; pr < P && ROT_PMAX * grp + pr < a.pairs; ++pr) {
+    // Thread t owns the cells of one (pair, slot): its row t / 16 + 48 i of
+    // 16 cells is bin (t / 16) / P + (48 / P) i, pair (t / 16) mod P.
+    {
+      const int pr = (tid >> 4) % P, bin0 = (tid >> 4) / P, fl = tid & (ROT_F - 1);
+      int2* to = stage + pr * ps + fl * ld;
+      const int64_t at0 = (int64_t)((ROT_PMAX * grp + pr) * ROT_F + fl) * B;
 #pragma unroll
       for (int i = 0; i < ROT_CPT; ++i) {
-        const int j64 = tid + ROT_THREADS * i;
-        const int row = j64 >> 4, bin = row / P, fl = j64 & (ROT_F - 1);
-        if (row - bin * P == pr && bin < B) stage[fl * (B + 1) + bin] = make_longlong2(tot[2 * i], tot[2 * i + 1]);
-      }
-      lds_barrier();
-      // features 0 .. FT-1 of the slice; a thin slice adds its R copies
-      for (int e = tid; e < FT * B; e += ROT_THREADS) {
-        const int fl = e / B, bin = e - fl * B;
-        longlong2 x = stage[fl * (B + 1) + bin];
-#pragma unroll
-        for (int rc = 1; rc < R; ++rc) {
-          const longlong2 y = stage[(fl + FT * rc) * (B + 1) + bin];
-          x.x += y.x;
-          x.y += y.y;
+        const int bin = bin0 + (ROT_ROWS / P) * i;
+        const int64_t x = sum_copies<FT>(tot[2 * i]), y = sum_copies<FT>(tot[2 * i + 1]);
+        const bool fx = fits_partial(x), fy = fits_partial(y);
+        if (bin < B && (FT == ROT_F || fl < FT)) {
+          to[bin] = make_int2(fx ? (int32_t)x : PART_ESC, fy ? (int32_t)y : PART_ESC);
+          if (!(fx && fy) && ROT_PMAX * grp + pr < a.pairs) dov[at0 + bin] = make_longlong2(x, y);
         }
-        const int64_t at = (int64_t)(ROT_PMAX * grp + pr) * ROT_F * B + e;
-        const bool fx = fits_partial(x.x), fy = fits_partial(x.y);
-        dst[at] = make_int2(fx ? (int32_t)x.x : PART_ESC, fy ? (int32_t)x.y : PART_ESC);
-        if (!(fx && fy)) dov[at] = x;
+        tot[2 * i] = 0;
+        tot[2 * i + 1] = 0;
       }
-      lds_barrier();
-    }
-#pragma unroll
-    for (int i = 0; i < ROT_CPT; ++i) {
-      lds64[tid + ROT_THREADS * i] = 0;
-      tot[2 * i] = 0;
-      tot[2 * i + 1] = 0;
     }
     lds_barrier();
+    // this channel group's pairs are pairs 3 grp .. 3 grp + P - 1 of the
+    // slot; pairs past the last (a short final group) and features past m
+    // have no reader and are not written
+    for (int rr = wave; rr < P * FT; rr += ROT_THREADS / 64) {
+      const int pr = rr / FT, fl = rr - pr * FT;
+      if (ROT_PMAX * grp + pr >= a.pairs || f0 + fl >= a.m) continue;
+      const int2* from = stage + pr * ps + fl * ld;
+      int2* out = dst + (int64_t)((ROT_PMAX * grp + pr) * ROT_F + fl) * B;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int bin = lane + 64 * u;
+        if (bin < B) out[bin] = from[bin];
+      }
+    }
+    if (vend < v1) {  // another node follows
+      lds_barrier();
+#pragma unroll
+      for (int i = 0; i < ROT_CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
+      lds_barrier();
+    }
     v = vend;
     ++p;
     while (p < a.n_build && a.pre[p + 1] <= v) ++p;
@@ -1127,7 +1156,7 @@ int32_t launch_build_histograms(const uint32_t* bins4, int64_t ld4, const uint8_
   hipEvent_t e0 = nullptr, e1 = nullptr;
   const bool prof = profile_on() && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
   if (prof) (void)hipEventRecord(e0, st);
-  const size_t lds_bytes = (size_t)ROT_CELLS * 8;
+  const size_t lds_bytes = ROT_LDS_BYTES;
   // up to six channels: one workgroup per (slice, row group); more: channel
   // groups of six (three pairs) each, one workgroup per (slice, group)
   switch (pl.c) {

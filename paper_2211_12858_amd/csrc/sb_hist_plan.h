@@ -41,6 +41,13 @@ constexpr int ROT_F = 16;
 constexpr int ROT_PMAX = 3;
 constexpr int ROT_CELLS = 256 * ROT_PMAX * ROT_F;
 constexpr int ROT_CPT = ROT_CELLS / ROT_THREADS;
+constexpr int ROT_ROWS = ROT_THREADS / ROT_F;  // rows of 16 cells that the workgroup touches at once
+static_assert(ROT_ROWS % 2 == 0 && ROT_ROWS % 3 == 0, "a thread's cells must share one pair");
+// Staging of a node's partials in the same LDS: rows of rot_stage_ld(n_bins)
+// int32 pairs, at most 258.
+constexpr int rot_stage_ld(int n_bins) { return (n_bins + 29) / 32 * 32 + 2; }
+constexpr int ROT_STAGE_PAIRS = ROT_PMAX * (ROT_F * rot_stage_ld(256) + 1);
+constexpr int ROT_LDS_BYTES = 8 * (ROT_STAGE_PAIRS > ROT_CELLS ? ROT_STAGE_PAIRS : ROT_CELLS);
 static_assert(ROT_CPT * ROT_THREADS == ROT_CELLS, "rotated cells must split evenly over the threads");
 static_assert(WINDOW_ROWS % ROT_THREADS == 0, "a fixed-point window must be a whole number of steps");
 
