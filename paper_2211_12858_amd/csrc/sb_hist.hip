@@ -550,8 +550,11 @@ __device__ inline void run_segment_rot(const HistArgs& a, lds_u64* lds, int64_t*
     r1 = r2;
     if (++steps == a.steps_per_window) {
       steps = 0;
+      // the second barrier keeps the next window's adds behind every fold
+      // read, so a cell's change between two reads is one window's rows
       lds_barrier();
       fold_cells<ROT_CPT, ROT_THREADS>((const uint64_t*)lds, tot);
+      lds_barrier();
     }
   }
 }
