@@ -503,46 +503,49 @@ __device__ inline void add_row_rot(lds_u64* lds, const RowRot<FT>& d, uint32_t r
   }
 }
 
-// Accumulate the lane's rows of virtual positions [v, vend) of one node
-// (segment start seg0, first virtual position pstart) into the LDS cells of
-// a rotated slice, folding into `tot` at every window.  HAS_IDX: rows come
+// A workgroup's rows of one node: virtual positions [v, vend), of which
+// position vs is position seg0 + (vs - pstart) of the level's rows.
+// Positions are 32-bit (every position and row is below 2^31, so unsigned
+// 32-bit sums of them do not wrap).
+struct Segment {
+  uint32_t v, vend, pstart, seg0;
+};
+
+// The lane's row at virtual position vs + lane_off.  HAS_IDX: rows come
 // through row_idx and are read from their records (otherwise the position is
-// the row of the contiguous data).  Positions are 32-bit (every position and
-// row is below 2^31, so unsigned 32-bit sums of them do not wrap).  The
-// row-index load of a lane is unconditional (positions past the end are
-// clamped into the segment and marked off), so the load path has no
-// branches.  The next step's row is loaded before the current one is added,
-// so its memory latency hides behind the current step's LDS work; the
-// prefetched row stays in flight across the window folds.
+// the row of the contiguous data).  The row-index load is unconditional
+// (positions past the end are clamped into the segment and marked off), so
+// the load path has no branches.
+template <bool HAS_IDX>
+__device__ inline RowRef row_at(const HistArgs& a, const Segment& sg, uint32_t vs, uint32_t lane_off) {
+  const uint32_t last_pos = sg.seg0 + (sg.vend - 1 - sg.pstart);
+  const uint32_t vv = vs + lane_off;
+  RowRef rr;
+  rr.on = vv < sg.vend;
+  uint32_t pos = sg.seg0 + (vv - sg.pstart);
+  pos = pos < last_pos ? pos : last_pos;
+  rr.raw = HAS_IDX ? a.row_idx[pos] : (int32_t)pos;
+  return rr;
+}
+
+// Accumulate the lane's rows of a segment into the LDS cells of a rotated
+// slice, folding into `tot` at every window.  The caller has loaded the rows
+// of the first two steps (r0, r1) and the first one's data (d0).  The next
+// step's row is loaded before the current one is added, so its memory latency
+// hides behind the current step's LDS work; the prefetched row stays in
+// flight across the window folds.
 template <int C, int FT, bool HAS_IDX>
-__device__ inline void run_segment_rot(const HistArgs& a, lds_u64* lds, int64_t* tot, uint32_t v,
-                                       uint32_t vend, uint32_t pstart, uint32_t seg0, int wave, int lane, int f0,
-                                       uint32_t B, int grp) {
-  // this workgroup's word of each quantised row (channel group grp)
-  const uint32_t* qbase = a.qrow + 4 * grp;
-  const uint32_t qstride = 4u * (uint32_t)a.cg;
-  constexpr uint32_t rows_step = ROT_THREADS;
-  const uint32_t last_pos = seg0 + (vend - 1 - pstart);
-  const uint32_t lane_off = (uint32_t)(wave * 64 + lane);
-  const uint32_t r = (uint32_t)lane & (FT - 1);
-  const uint32_t slot0 = FT < ROT_F ? (((uint32_t)lane / FT) & (ROT_F / FT - 1)) * FT : 0u;
-  auto row_at = [&](uint32_t vs) -> RowRef {
-    const uint32_t vv = vs + lane_off;
-    RowRef rr;
-    rr.on = vv < vend;
-    uint32_t pos = seg0 + (vv - pstart);
-    pos = pos < last_pos ? pos : last_pos;
-    rr.raw = HAS_IDX ? a.row_idx[pos] : (int32_t)pos;
-    return rr;
-  };
-  RowRef r0 = row_at(v);
-  RowRef r1 = row_at(v + rows_step);
-  RowRot<FT> d0, d1;
-  load_row_rot<FT, HAS_IDX>(a, r0, f0, qbase, qstride, d0);
+__device__ inline void run_segment_rot(const HistArgs& a, lds_u64* lds, int64_t* tot, const Segment& sg, RowRef r0,
+                                       RowRef r1, RowRot<FT> d0, uint32_t lane_off, int f0, uint32_t B,
+                                       const uint32_t* qbase, uint32_t qstride) {
+  const uint32_t lane = lane_off & 63;
+  const uint32_t r = lane & (FT - 1);
+  const uint32_t slot0 = FT < ROT_F ? ((lane / FT) & (ROT_F / FT - 1)) * FT : 0u;
+  RowRot<FT> d1;
   int steps = 0;
 #pragma unroll 1
-  for (uint32_t vs = v; vs < vend; vs += rows_step) {
-    const RowRef r2 = row_at(vs + 2 * rows_step);
+  for (uint32_t vs = sg.v; vs < sg.vend; vs += ROT_THREADS) {
+    const RowRef r2 = row_at<HAS_IDX>(a, sg, vs + 2 * ROT_THREADS, lane_off);
     load_row_rot<FT, HAS_IDX>(a, r1, f0, qbase, qstride, d1);
     if (r0.on) add_row_rot<C, FT>(lds, d0, r, slot0, B);
     r0 = r1;
@@ -586,7 +589,7 @@ __device__ inline int64_t sum_copies(int64_t x) {
 // a level of 64 built nodes x 200 features x 11 channels.)
 // Slice s of FT features (16, or a thin slice's f_thin), row group q of
 // qn: the rows of virtual positions [q T / qn, (q+1) T / qn).
-template <int C, int FT>
+template <int C, int FT, bool HAS_IDX>
 __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds64, int s, int grp, int q, int qn) {
   constexpr int P = (C + 1) / 2;
   const int64_t T = a.pre[a.n_build];
@@ -601,43 +604,59 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
     else hi = mid;
   }
   int p = lo;
+  // this workgroup's rows of built node p, from virtual position v on
+  auto segment = [&](int pp, int64_t v) {
+    const int64_t pstart = a.pre[pp], pend = a.pre[pp + 1];
+    const int64_t seg0 = clamp_i32(a.node_off[node_of(a, pp)], 0, a.n);
+    return Segment{(uint32_t)v, (uint32_t)(v1 < pend ? v1 : pend), (uint32_t)pstart, (uint32_t)seg0};
+  };
 
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   const int f0 = s * ROT_F;
   const int B = a.n_bins;
+  // this workgroup's word of each quantised row (channel group grp)
+  const uint32_t* qbase = a.qrow + 4 * grp;
+  const uint32_t qstride = 4u * (uint32_t)a.cg;
 
+  Segment sg = segment(p, v0);
+  RowRef r0 = row_at<HAS_IDX>(a, sg, sg.v, tid), r1 = row_at<HAS_IDX>(a, sg, sg.v + ROT_THREADS, tid);
   int64_t tot[2 * ROT_CPT];
 #pragma unroll
   for (int jj = 0; jj < 2 * ROT_CPT; ++jj) tot[jj] = 0;
 #pragma unroll
   for (int i = 0; i < ROT_CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
-  __syncthreads();
+  RowRot<FT> d0;
+  load_row_rot<FT, HAS_IDX>(a, r0, f0, qbase, qstride, d0);
+  lds_barrier();
 
   // staging of a node's partials: int32 channel pairs [pair][feature][bin] in
   // rows of ld, ld mod 32 == 2, and pairs ps apart, so that the 16 features x
   // 4 (bin, pair) rows that a wave writes at once spread over the banks
   int2* stage = reinterpret_cast<int2*>(lds64);
   const int ld = rot_stage_ld(B), ps = ROT_F * ld + 1;
-  int64_t v = v0;
-  while (v < v1) {
-    const int32_t j = node_of(a, p);
-    const int64_t pstart = a.pre[p];
-    const int64_t vend = v1 < a.pre[p + 1] ? v1 : a.pre[p + 1];
-    const int64_t seg0 = clamp_i32(a.node_off[j], 0, a.n);
-    lds_u64* L = (lds_u64*)lds64;  // generic to LDS address space: 32-bit offsets
-    if (a.row_idx)
-      run_segment_rot<C, FT, true>(a, L, tot, (uint32_t)v, (uint32_t)vend, (uint32_t)pstart, (uint32_t)seg0, wave,
-                                   lane, f0, (uint32_t)B, grp);
-    else
-      run_segment_rot<C, FT, false>(a, L, tot, (uint32_t)v, (uint32_t)vend, (uint32_t)pstart, (uint32_t)seg0,
-                                    wave, lane, f0, (uint32_t)B, grp);
+  for (;;) {
+    run_segment_rot<C, FT, HAS_IDX>(a, (lds_u64*)lds64, tot, sg, r0, r1, d0, (uint32_t)tid, f0, (uint32_t)B, qbase,
+                                    qstride);
+    // the next node's offsets and first rows are read while this node's
+    // partials go out: its chain of dependent loads (prefix, node, offsets,
+    // row index, row) would otherwise start after them
+    const bool more = sg.vend < v1;  // uniform
+    const int pend = p;
+    if (more) {
+      const int64_t v = sg.vend;
+      ++p;
+      while (p < a.n_build && a.pre[p + 1] <= v) ++p;
+      sg = segment(p, v);
+      r0 = row_at<HAS_IDX>(a, sg, sg.v, tid);
+      r1 = row_at<HAS_IDX>(a, sg, sg.v + ROT_THREADS, tid);
+    }
     // The node-end barriers wait for LDS operations only: the partial stores
     // take their data from registers, so nothing here waits for them.
     lds_barrier();
     fold_cells<ROT_CPT, ROT_THREADS>(lds64, tot);
     lds_barrier();  // every fold read is done: the LDS becomes the staging area
-    const int64_t slot = ((int64_t)s * a.slots + q + p) * a.cells;  // channel cells
+    const int64_t slot = ((int64_t)s * a.slots + q + pend) * a.cells;  // channel cells
     int2* dst = reinterpret_cast<int2*>(a.part32 + slot);
     longlong2* dov = reinterpret_cast<longlong2*>(a.ovf + slot);
     // Thread t owns the cells of one (pair, slot): its row t / 16 + 48 i of
@@ -659,6 +678,7 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
         tot[2 * i + 1] = 0;
       }
     }
+    if (more) load_row_rot<FT, HAS_IDX>(a, r0, f0, qbase, qstride, d0);
     lds_barrier();
     // this channel group's pairs are pairs 3 grp .. 3 grp + P - 1 of the
     // slot; pairs past the last (a short final group) and features past m
@@ -674,15 +694,11 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
         if (bin < B) out[bin] = from[bin];
       }
     }
-    if (vend < v1) {  // another node follows
-      lds_barrier();
+    if (!more) return;
+    lds_barrier();
 #pragma unroll
-      for (int i = 0; i < ROT_CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
-      lds_barrier();
-    }
-    v = vend;
-    ++p;
-    while (p < a.n_build && a.pre[p + 1] <= v) ++p;
+    for (int i = 0; i < ROT_CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
+    lds_barrier();
   }
 }
 
@@ -701,18 +717,21 @@ k_hist_rot(HistArgs a) {
   if (g < nfull) {
     const int q = (g / uf) * 8 + xcd;
     const int u = g % uf;
-    if (q < a.q) hist_rot_group<C, ROT_F>(a, lds64, u / a.cg, u % a.cg, q, a.q);
+    if (q >= a.q) return;
+    if (a.row_idx) hist_rot_group<C, ROT_F, true>(a, lds64, u / a.cg, u % a.cg, q, a.q);
+    else hist_rot_group<C, ROT_F, false>(a, lds64, u / a.cg, u % a.cg, q, a.q);
     return;
   }
+  // a thin slice: only for rows read straight from the data
   const int t = g - nfull;
   const int q = (t / a.cg) * 8 + xcd, grp = t % a.cg;
   if (!a.f_thin || q >= a.q_thin) return;
   const int s = a.slices_full;
   switch (a.f_thin) {
-    case 1: hist_rot_group<C, 1>(a, lds64, s, grp, q, a.q_thin); break;
-    case 2: hist_rot_group<C, 2>(a, lds64, s, grp, q, a.q_thin); break;
-    case 4: hist_rot_group<C, 4>(a, lds64, s, grp, q, a.q_thin); break;
-    default: hist_rot_group<C, 8>(a, lds64, s, grp, q, a.q_thin); break;
+    case 1: hist_rot_group<C, 1, false>(a, lds64, s, grp, q, a.q_thin); break;
+    case 2: hist_rot_group<C, 2, false>(a, lds64, s, grp, q, a.q_thin); break;
+    case 4: hist_rot_group<C, 4, false>(a, lds64, s, grp, q, a.q_thin); break;
+    default: hist_rot_group<C, 8, false>(a, lds64, s, grp, q, a.q_thin); break;
   }
 }
 
