@@ -37,6 +37,31 @@
 
 namespace sb {
 
+// Row groups of uf workgroups each, one workgroup per CU at a time.  All that
+// fit at once (256 / uf) where that is at least one; wide matrices may take up
+// to 8 over several rounds of workgroups, if the last round is so much fuller
+// that the rounds per row group drop.
+static int row_groups(int uf) {
+  int best_q = HIST_CUS / uf > 0 ? HIST_CUS / uf : 1;
+  double best = (double)((best_q * uf + HIST_CUS - 1) / HIST_CUS) / best_q;
+  for (int qq = best_q + 1; qq <= 8; ++qq) {
+    const double cost = (double)((qq * uf + HIST_CUS - 1) / HIST_CUS) / qq;
+    if (cost < 0.95 * best) {
+      best = cost;
+      best_q = qq;
+    }
+  }
+  return best_q;
+}
+
+// Work of one row of a thin slice of f features, in features of a full slice:
+// its loads and unpacking cost about 6 (a step of 768 rows without any adds
+// takes 0.85 us, a full slice's 2 us), more adds than that their share.  With
+// f alone as its cost, 200,000 rows x 50 features gave the 2-feature slice 13
+// of 256 workgroups, and the root took 32 us instead of 17; with more than 6,
+// the root of 1M x 99 x 21 channels 284 instead of 255 us.
+static double thin_row_cost(int f) { return fmax(6.0, 2.0 + 0.875 * f); }
+
 HistPlan hist_plan(int32_t m, int32_t n_bins, int32_t k, int32_t n_build, bool thin_ok) {
   HistPlan p{};
   p.c = k + 1;
@@ -56,34 +81,34 @@ HistPlan hist_plan(int32_t m, int32_t n_bins, int32_t k, int32_t n_build, bool t
       else p.f_thin = ft;
     }
     p.slices = p.slices_full + (p.f_thin ? 1 : 0);
-    const int S = p.slices_full, cus = HIST_CUS_PER_XCD;
+    const int S = p.slices_full;
     const int uf = S * p.cg, ut = p.cg;  // workgroups per full / thin row group
     if (!p.f_thin) {
-      p.a_full = cus / uf > 0 ? cus / uf : 1;
-      p.b_thin = 0;
+      p.q = row_groups(uf);
+      p.q_thin = 0;
     } else if (S == 0) {
-      p.a_full = 0;
-      p.b_thin = cus / ut > 0 ? cus / ut : 1;
+      p.q = 0;
+      p.q_thin = row_groups(ut);
+    } else if (uf > HIST_CUS / 2) {
+      p.q = p.q_thin = row_groups(uf);
     } else {
-      // per-workgroup work of a full slice is ROT_F rows-steps per row of its
-      // group, of the thin slice f_thin: minimise the larger of the two
-      int best_a = 1;
+      // a row costs a workgroup of a full slice ROT_F units of adds and one of
+      // the thin slice thin_row_cost: minimise the larger workgroup's work,
+      // with the thin slice on the CUs that the full ones leave on each XCD
       double best = 1e30;
-      for (int aa = 1; aa * uf < cus || aa == 1; ++aa) {
-        const int bb = (cus - aa * uf) / ut > 0 ? (cus - aa * uf) / ut : 1;
-        const double cost = fmax((double)ROT_F / aa, (double)p.f_thin / bb);
+      for (int qq = 1; qq * uf <= HIST_CUS; ++qq) {
+        const int qt = (HIST_CUS / 8 - (qq * uf + 7) / 8) * 8 / ut;
+        if (qt < 1) break;
+        const double cost = fmax((double)ROT_F / qq, thin_row_cost(p.f_thin) / qt);
         if (cost < best) {
           best = cost;
-          best_a = aa;
+          p.q = qq;
+          p.q_thin = qt;
         }
       }
-      p.a_full = best_a;
-      p.b_thin = (cus - best_a * uf) / ut > 0 ? (cus - best_a * uf) / ut : 1;
     }
-    p.q = 8 * p.a_full;
-    p.q_thin = 8 * p.b_thin;
     p.slots = (int64_t)(p.q > p.q_thin ? p.q : p.q_thin) + n_build;
-    p.grid = 8 * (p.a_full * uf + p.b_thin * ut);
+    p.grid = 8 * ((p.q * uf + 7) / 8 + (p.q_thin * ut + 7) / 8);
     return p;
   }
   return p;  // more than ROT_MAX_C channels or 256 bins: unsupported (nq = 0)
@@ -132,7 +157,7 @@ struct HistArgs {
   int32_t m, n_bins, c, pairs, n_nodes, n_build;
   int32_t f, slices, cells, q, steps_per_window;
   int64_t slots;
-  int32_t slices_full, f_thin, a_full, b_thin, q_thin, cg;  // rotated kernel plan (see HistPlan)
+  int32_t slices_full, f_thin, q_thin, cg;  // rotated kernel plan (see HistPlan)
 };
 
 // Row groups of slice s (the thin slice has its own count).
@@ -702,36 +727,39 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
   }
 }
 
-// The histogram kernel.  Workgroup b runs on XCD b % 8; on each XCD the
-// first a_full * slices_full * cg workgroups take the (full slice, channel
-// group) pairs of a_full row groups (so the slices of a row group share the
-// XCD's L2) and the next b_thin * cg the thin slice.
+// The histogram kernel.  Workgroup b runs on XCD b % 8.  The units (row group,
+// full slice, channel group) are numbered row group first, and each XCD takes
+// an eighth of them in one run, so the slices of a row group share an XCD's L2
+// (a row group at the border of two XCDs is read into both); then an eighth of
+// the thin slice's.
 template <int C>
 __global__ void __launch_bounds__(ROT_THREADS)
 k_hist_rot(HistArgs a) {
   extern __shared__ uint64_t lds64[];
   const int b = blockIdx.x;
   const int xcd = b & 7, g = b >> 3;
-  const int uf = a.slices_full * a.cg;  // workgroups per full row group: (slice, channel group)
-  const int nfull = a.a_full * uf;
-  if (g < nfull) {
-    const int q = (g / uf) * 8 + xcd;
-    const int u = g % uf;
-    if (q >= a.q) return;
-    if (a.row_idx) hist_rot_group<C, ROT_F, true>(a, lds64, u / a.cg, u % a.cg, q, a.q);
-    else hist_rot_group<C, ROT_F, false>(a, lds64, u / a.cg, u % a.cg, q, a.q);
+  const int uf = a.slices_full * a.cg;  // units per full row group: (slice, channel group)
+  const int qf = a.q, qt = a.q_thin;
+  const int nfull = qf * uf, nthin = a.f_thin ? qt * a.cg : 0;
+  const int per = (nfull + 7) >> 3, per_thin = (nthin + 7) >> 3;  // units of an XCD
+  if (g < per) {
+    const int w = xcd * per + g;
+    const int q = w / uf, u = w % uf;
+    if (q >= qf) return;
+    if (a.row_idx) hist_rot_group<C, ROT_F, true>(a, lds64, u / a.cg, u % a.cg, q, qf);
+    else hist_rot_group<C, ROT_F, false>(a, lds64, u / a.cg, u % a.cg, q, qf);
     return;
   }
-  // a thin slice: only for rows read straight from the data
-  const int t = g - nfull;
-  const int q = (t / a.cg) * 8 + xcd, grp = t % a.cg;
-  if (!a.f_thin || q >= a.q_thin) return;
+  // the thin slice: only for rows read straight from the data
+  const int t = xcd * per_thin + (g - per);
+  if (g - per >= per_thin || t >= nthin) return;
+  const int q = t / a.cg, grp = t % a.cg;
   const int s = a.slices_full;
   switch (a.f_thin) {
-    case 1: hist_rot_group<C, 1, false>(a, lds64, s, grp, q, a.q_thin); break;
-    case 2: hist_rot_group<C, 2, false>(a, lds64, s, grp, q, a.q_thin); break;
-    case 4: hist_rot_group<C, 4, false>(a, lds64, s, grp, q, a.q_thin); break;
-    default: hist_rot_group<C, 8, false>(a, lds64, s, grp, q, a.q_thin); break;
+    case 1: hist_rot_group<C, 1, false>(a, lds64, s, grp, q, qt); break;
+    case 2: hist_rot_group<C, 2, false>(a, lds64, s, grp, q, qt); break;
+    case 4: hist_rot_group<C, 4, false>(a, lds64, s, grp, q, qt); break;
+    default: hist_rot_group<C, 8, false>(a, lds64, s, grp, q, qt); break;
   }
 }
 
@@ -1166,8 +1194,6 @@ int32_t launch_build_histograms(const uint32_t* bins4, int64_t ld4, const uint8_
   a.q = pl.q;
   a.slices_full = pl.slices_full;
   a.f_thin = pl.f_thin;
-  a.a_full = pl.a_full;
-  a.b_thin = pl.b_thin;
   a.q_thin = pl.q_thin;
   a.cg = pl.cg;
   a.steps_per_window = WINDOW_ROWS / ROT_THREADS;

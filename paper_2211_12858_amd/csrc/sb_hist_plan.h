@@ -33,7 +33,7 @@ static_assert(QBITS + 2 <= QFIELD_BITS, "a quantised value of magnitude <= 2^QBI
 
 // ---------------------------------------------------------------- histogram plan
 // MI355X: 8 XCDs of 32 CUs; workgroup b is dispatched to XCD b % 8.
-constexpr int HIST_CUS_PER_XCD = 32;
+constexpr int HIST_CUS = 256;
 
 // One histogram workgroup: 768 threads (12 waves, 3 per SIMD) and the cells
 // of a slice of 16 features for up to 3 channel pairs (c <= 6), laid out
@@ -67,17 +67,19 @@ struct HistPlan {
   // m is not a multiple of 16 the rest go to one thin slice of f_thin
   // features (a power of two below 16), whose workgroups keep 16 / f_thin
   // copies of each cell so that its adds stay conflict-free while a row
-  // costs f_thin steps instead of 16.  Per XCD: a_full row groups of every
-  // full slice and b_thin row groups of the thin slice (q = 8 a_full,
-  // q_thin = 8 b_thin), chosen to even out the work of its 32 CUs.  Only for
-  // rows read straight from the data (the root): rows gathered through row
+  // costs f_thin steps instead of 16: q row groups of every full
+  // slice and q_thin of the thin slice, chosen to even out the work of the
+  // 256 CUs.  Only for rows read straight from the data (the root): rows gathered through row
   // indices are cheaper to read when the slices of a row group share an XCD,
   // so there the last slice is a padded slice of 16 like the others.
-  int slices_full, f_thin, a_full, b_thin, q_thin;
+  int slices_full, f_thin, q_thin;
   // Rotated kernel with c > 6 channels: cg = ceil(c / 6) channel groups of
   // at most three pairs; every (slice, channel group) of a row group is one
   // workgroup, and all groups of a slice write the same partial slots.
   int cg;
+  // Workgroups: q * slices_full * cg of the full slices and q_thin * cg of the
+  // thin one, an eighth to each XCD.  Row groups need not be a multiple of the
+  // XCDs: 7 slices take 36 row groups (252 CUs), where 4 per XCD take 224.
   int grid;       // histogram workgroups
 };
 // Plan of one histogram launch; nq == 0 when c > ROT_MAX_C or n_bins > 256.
