@@ -160,9 +160,18 @@ struct HistArgs {
   int32_t slices_full, f_thin, q_thin, cg;  // rotated kernel plan (see HistPlan)
 };
 
-// Row groups of slice s (the thin slice has its own count).
-__device__ inline int32_t groups_of(const HistArgs& a, int s) {
-  return (a.f_thin && s >= a.slices_full) ? a.q_thin : a.q;
+// Row groups in use, of at most q, for T rows: no group holds fewer than
+// GROUP_MIN_ROWS.  A row group costs a start, a node end and its partials'
+// write and read whatever its rows.
+__device__ inline int32_t groups_in_use(int32_t q, int64_t T) {
+  const int64_t most = (T + GROUP_MIN_ROWS - 1) / GROUP_MIN_ROWS;
+  return most < 1 ? 1 : (most < q ? (int32_t)most : q);
+}
+
+// Row groups of slice s (the thin slice has its own count) on a level of T
+// built rows.
+__device__ inline int32_t groups_of(const HistArgs& a, int s, int64_t T) {
+  return groups_in_use((a.f_thin && s >= a.slices_full) ? a.q_thin : a.q, T);
 }
 
 __device__ inline int32_t clamp_i32(int64_t v, int64_t lo, int64_t hi) {
@@ -615,9 +624,9 @@ __device__ inline int64_t sum_copies(int64_t x) {
 // Slice s of FT features (16, or a thin slice's f_thin), row group q of
 // qn: the rows of virtual positions [q T / qn, (q+1) T / qn).
 template <int C, int FT, bool HAS_IDX>
-__device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds64, int s, int grp, int q, int qn) {
+__device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds64, int64_t T, int s, int grp, int q,
+                                               int qn) {
   constexpr int P = (C + 1) / 2;
-  const int64_t T = a.pre[a.n_build];
   const int64_t v0 = (int64_t)q * T / qn;
   const int64_t v1 = (int64_t)(q + 1) * T / qn;
   if (v0 >= v1) return;
@@ -732,6 +741,8 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
 // an eighth of them in one run, so the slices of a row group share an XCD's L2
 // (a row group at the border of two XCDs is read into both); then an eighth of
 // the thin slice's.
+// Levels of few rows use fewer row groups than planned (spread over the XCDs
+// alike); the other workgroups end at once.
 template <int C>
 __global__ void __launch_bounds__(ROT_THREADS)
 k_hist_rot(HistArgs a) {
@@ -739,15 +750,16 @@ k_hist_rot(HistArgs a) {
   const int b = blockIdx.x;
   const int xcd = b & 7, g = b >> 3;
   const int uf = a.slices_full * a.cg;  // units per full row group: (slice, channel group)
-  const int qf = a.q, qt = a.q_thin;
+  const int64_t T = a.pre[a.n_build];
+  const int qf = groups_in_use(a.q, T), qt = groups_in_use(a.q_thin, T);
   const int nfull = qf * uf, nthin = a.f_thin ? qt * a.cg : 0;
   const int per = (nfull + 7) >> 3, per_thin = (nthin + 7) >> 3;  // units of an XCD
   if (g < per) {
     const int w = xcd * per + g;
     const int q = w / uf, u = w % uf;
     if (q >= qf) return;
-    if (a.row_idx) hist_rot_group<C, ROT_F, true>(a, lds64, u / a.cg, u % a.cg, q, qf);
-    else hist_rot_group<C, ROT_F, false>(a, lds64, u / a.cg, u % a.cg, q, qf);
+    if (a.row_idx) hist_rot_group<C, ROT_F, true>(a, lds64, T, u / a.cg, u % a.cg, q, qf);
+    else hist_rot_group<C, ROT_F, false>(a, lds64, T, u / a.cg, u % a.cg, q, qf);
     return;
   }
   // the thin slice: only for rows read straight from the data
@@ -756,10 +768,10 @@ k_hist_rot(HistArgs a) {
   const int q = t / a.cg, grp = t % a.cg;
   const int s = a.slices_full;
   switch (a.f_thin) {
-    case 1: hist_rot_group<C, 1, false>(a, lds64, s, grp, q, qt); break;
-    case 2: hist_rot_group<C, 2, false>(a, lds64, s, grp, q, qt); break;
-    case 4: hist_rot_group<C, 4, false>(a, lds64, s, grp, q, qt); break;
-    default: hist_rot_group<C, 8, false>(a, lds64, s, grp, q, qt); break;
+    case 1: hist_rot_group<C, 1, false>(a, lds64, T, s, grp, q, qt); break;
+    case 2: hist_rot_group<C, 2, false>(a, lds64, T, s, grp, q, qt); break;
+    case 4: hist_rot_group<C, 4, false>(a, lds64, T, s, grp, q, qt); break;
+    default: hist_rot_group<C, 8, false>(a, lds64, T, s, grp, q, qt); break;
   }
 }
 
@@ -789,13 +801,11 @@ __global__ void __launch_bounds__(256) k_hist_reduce(HistArgs a) {
   const int64_t lo = a.pre[p], hi = a.pre[p + 1];
   int64_t sum = 0;
   if (hi > lo) {
-    const int32_t qn = groups_of(a, s);
+    const int32_t qn = groups_of(a, s, T);
     const int64_t qlo = group_of(lo, T, qn), qhi = group_of(hi - 1, T, qn);
     const int64_t base = ((int64_t)s * a.slots + p) * a.cells + e;
     const int32_t* src = a.part32 + base;
     const int64_t* ov = a.ovf + base;
-    const bool dense = T >= qn;  // every row group holds at least one position
-    auto live = [&](int64_t q) { return q <= qhi && (dense || q * T / qn < (q + 1) * T / qn); };
     // batches of eight row groups, loads unconditional (clamped to the last
     // group, dropped past it); escapes are flagged, and a thread that met one
     // sums again with the overflow slots
@@ -806,18 +816,17 @@ __global__ void __launch_bounds__(256) k_hist_reduce(HistArgs a) {
       for (int u = 0; u < 8; ++u) v[u] = src[(q + u <= qhi ? q + u : qhi) * a.cells];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const bool use = live(q + u);
+        const bool use = q + u <= qhi;  // (no row group is empty: qn <= T)
         sum += use ? v[u] : 0;
         esc |= use && v[u] == PART_ESC;
       }
     }
     if (esc) {
       sum = 0;
-      for (int64_t q = qlo; q <= qhi; ++q)
-        if (live(q)) {
-          const int32_t x = src[q * a.cells];
-          sum += x == PART_ESC ? ov[q * a.cells] : (int64_t)x;
-        }
+      for (int64_t q = qlo; q <= qhi; ++q) {
+        const int32_t x = src[q * a.cells];
+        sum += x == PART_ESC ? ov[q * a.cells] : (int64_t)x;
+      }
     }
   }
   const int64_t cpn = (int64_t)a.m * a.c * a.n_bins;
@@ -903,13 +912,12 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
   const int64_t cpn = (int64_t)a.m * c * B;
   const int64_t T = a.pre[a.n_build];
   const int64_t lo = a.pre[p], hi = a.pre[p + 1];
-  const int32_t qn = groups_of(a, s);
+  const int32_t qn = groups_of(a, s, T);
   const int64_t nlo = hi > lo ? group_of(lo, T, qn) : 0, nhi = hi > lo ? group_of(hi - 1, T, qn) : -1;
   // this thread's quarter of the node's row groups [nlo, nhi]
   const int64_t per = (nhi - nlo + RQ) / RQ;
   const int64_t qlo = nlo + quarter * per;
   const int64_t qhi = (qlo + per - 1 < nhi) ? qlo + per - 1 : nhi;
-  const bool dense = T >= qn;  // every row group holds at least one position
   // The parent's values for the sibling, loaded first so that this read and
   // the partials' are in flight together (a block reads them once each).
   double hp[2 * PMAX];
@@ -934,53 +942,36 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
     const int2* src = reinterpret_cast<const int2*>(a.part32 + base) + e64;
     const longlong2* ov = reinterpret_cast<const longlong2*>(a.ovf + base) + e64;
     const int64_t stride = a.cells / 2;  // one row group, in channel pairs
-    auto live = [&](int64_t q) { return q <= qhi && (dense || q * T / qn < (q + 1) * T / qn); };
     bool esc = false;
-    if (dense) {
-      constexpr int BQ = PMAX <= 4 ? 4 : 2;
-      auto load = [&](int64_t q0, int2 (&v)[BQ][PMAX]) {
+    constexpr int BQ = PMAX <= 4 ? 4 : 2;
+    auto load = [&](int64_t q0, int2 (&v)[BQ][PMAX]) {
 #pragma unroll
-        for (int u = 0; u < BQ; ++u)
+      for (int u = 0; u < BQ; ++u)
 #pragma unroll
-          for (int pr = 0; pr < PMAX; ++pr)
-            v[u][pr] = src[(q0 + u <= qhi ? q0 + u : qhi) * stride + (int64_t)(pr < a.pairs ? pr : a.pairs - 1) * FB];
-      };
-      auto add = [&](int64_t q0, const int2 (&v)[BQ][PMAX]) {
+        for (int pr = 0; pr < PMAX; ++pr)
+          v[u][pr] = src[(q0 + u <= qhi ? q0 + u : qhi) * stride + (int64_t)(pr < a.pairs ? pr : a.pairs - 1) * FB];
+    };
+    auto add = [&](int64_t q0, const int2 (&v)[BQ][PMAX]) {
 #pragma unroll
-        for (int u = 0; u < BQ; ++u)
-#pragma unroll
-          for (int pr = 0; pr < PMAX; ++pr) {
-            const bool use = q0 + u <= qhi && pr < a.pairs;
-            const int2 x = v[u][pr];
-            acc_lo[pr] += use ? x.x : 0;
-            acc_hi[pr] += use ? x.y : 0;
-            esc |= use && (x.x == PART_ESC || x.y == PART_ESC);
-          }
-      };
-      for (int64_t q = qlo; q <= qhi; q += BQ) {
-        int2 vq[BQ][PMAX];
-        load(q, vq);
-        add(q, vq);
-      }
-    } else {
-      // fewer positions than row groups (tiny levels): empty groups wrote nothing
-      for (int64_t q = qlo; q <= qhi; ++q) {
-        if (!live(q)) continue;
+      for (int u = 0; u < BQ; ++u)
 #pragma unroll
         for (int pr = 0; pr < PMAX; ++pr) {
-          if (pr >= a.pairs) continue;
-          const int2 x = src[q * stride + (int64_t)pr * FB];
-          acc_lo[pr] += x.x;
-          acc_hi[pr] += x.y;
-          esc |= x.x == PART_ESC || x.y == PART_ESC;
+          const bool use = q0 + u <= qhi && pr < a.pairs;
+          const int2 x = v[u][pr];
+          acc_lo[pr] += use ? x.x : 0;
+          acc_hi[pr] += use ? x.y : 0;
+          esc |= use && (x.x == PART_ESC || x.y == PART_ESC);
         }
-      }
+    };
+    for (int64_t q = qlo; q <= qhi; q += BQ) {
+      int2 vq[BQ][PMAX];
+      load(q, vq);
+      add(q, vq);
     }
     if (esc) {
 #pragma unroll
       for (int pr = 0; pr < PMAX; ++pr) acc_lo[pr] = acc_hi[pr] = 0;
       for (int64_t q = qlo; q <= qhi; ++q) {
-        if (!live(q)) continue;
         for (int pr = 0; pr < PMAX && pr < a.pairs; ++pr) {
           const int2 x = src[q * stride + (int64_t)pr * FB];
           if (x.x == PART_ESC || x.y == PART_ESC) {

@@ -34,6 +34,10 @@ static_assert(QBITS + 2 <= QFIELD_BITS, "a quantised value of magnitude <= 2^QBI
 // ---------------------------------------------------------------- histogram plan
 // MI355X: 8 XCDs of 32 CUs; workgroup b is dispatched to XCD b % 8.
 constexpr int HIST_CUS = 256;
+// A row group holds at least one step's rows (see groups_in_use): with all 256
+// row groups, a tree on 10,000 rows x 10 features took 174 us, with at least
+// 768 rows 110, 1152 rows 113, 1536 rows 116 and 2304 rows 117 us.
+constexpr int GROUP_MIN_ROWS = 768;
 
 // One histogram workgroup: 768 threads (12 waves, 3 per SIMD) and the cells
 // of a slice of 16 features for up to 3 channel pairs (c <= 6), laid out
