@@ -823,9 +823,17 @@ __global__ void __launch_bounds__(256) k_hist_reduce(HistArgs a) {
     }
     if (esc) {
       sum = 0;
-      for (int64_t q = qlo; q <= qhi; ++q) {
-        const int32_t x = src[q * a.cells];
-        sum += x == PART_ESC ? ov[q * a.cells] : (int64_t)x;
+      for (int64_t q = qlo; q <= qhi; q += 8) {
+        int32_t v[8];
+        int64_t o[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int64_t at = (q + u <= qhi ? q + u : qhi) * a.cells;
+          v[u] = src[at];
+          o[u] = ov[at];  // unspecified where v fits; not used there
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += q + u <= qhi ? (v[u] == PART_ESC ? o[u] : (int64_t)v[u]) : 0;
       }
     }
   }
@@ -930,9 +938,11 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
   // int32 partials.  Fast path: batches of BQ row groups and every channel
   // pair, loads unconditional (groups past the node's last and pairs past
   // the last repeat it; the extra values are dropped), no branch on the
-  // values: escapes are only flagged.  A lane that met an escape sums its
-  // bin again with the overflow slots (rare: a workgroup's sum of one bin
-  // must pass 2^31).
+  // values: escapes are only flagged, by pair.  A lane that met one sums that
+  // pair again with the overflow slots, four row groups in flight (features
+  // of few levels escape at the first levels of large data: a workgroup's sum
+  // of one bin passes 2^31.  One load after another, this took the root's
+  // level end of 2M x 100 from 14 to 38 us).
   int64_t acc_lo[PMAX], acc_hi[PMAX];
 #pragma unroll
   for (int pr = 0; pr < PMAX; ++pr) acc_lo[pr] = acc_hi[pr] = 0;
@@ -942,7 +952,7 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
     const int2* src = reinterpret_cast<const int2*>(a.part32 + base) + e64;
     const longlong2* ov = reinterpret_cast<const longlong2*>(a.ovf + base) + e64;
     const int64_t stride = a.cells / 2;  // one row group, in channel pairs
-    bool esc = false;
+    uint32_t esc = 0;  // pairs that met an escape
     constexpr int BQ = PMAX <= 4 ? 4 : 2;
     auto load = [&](int64_t q0, int2 (&v)[BQ][PMAX]) {
 #pragma unroll
@@ -960,7 +970,7 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
           const int2 x = v[u][pr];
           acc_lo[pr] += use ? x.x : 0;
           acc_hi[pr] += use ? x.y : 0;
-          esc |= use && (x.x == PART_ESC || x.y == PART_ESC);
+          esc |= use && (x.x == PART_ESC || x.y == PART_ESC) ? 1u << pr : 0u;
         }
     };
     for (int64_t q = qlo; q <= qhi; q += BQ) {
@@ -968,21 +978,34 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
       load(q, vq);
       add(q, vq);
     }
-    if (esc) {
+    // (a loop over the pairs rather than unrolled, and four groups in flight:
+    // unrolled with eight, it took the 3-pair kernel from 78 to 129 registers
+    // and the deep levels, which never escape, from 20 to 25 us)
+    while (esc) {
+      const int pr = __ffs(esc) - 1;
+      esc &= esc - 1;
+      int64_t sl = 0, sh = 0;
+#pragma unroll 1
+      for (int64_t q = qlo; q <= qhi; q += 4) {
+        int2 x[4];
+        longlong2 o[4];
 #pragma unroll
-      for (int pr = 0; pr < PMAX; ++pr) acc_lo[pr] = acc_hi[pr] = 0;
-      for (int64_t q = qlo; q <= qhi; ++q) {
-        for (int pr = 0; pr < PMAX && pr < a.pairs; ++pr) {
-          const int2 x = src[q * stride + (int64_t)pr * FB];
-          if (x.x == PART_ESC || x.y == PART_ESC) {
-            const longlong2 o = ov[q * stride + (int64_t)pr * FB];
-            acc_lo[pr] += o.x;
-            acc_hi[pr] += o.y;
-          } else {
-            acc_lo[pr] += x.x;
-            acc_hi[pr] += x.y;
-          }
+        for (int u = 0; u < 4; ++u) {
+          const int64_t at = (q + u <= qhi ? q + u : qhi) * stride + (int64_t)pr * FB;
+          x[u] = src[at];
+          o[u] = ov[at];  // unspecified where both sums fit; not used there
         }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const bool use = q + u <= qhi, over = x[u].x == PART_ESC || x[u].y == PART_ESC;
+          sl += use ? (over ? o[u].x : (int64_t)x[u].x) : 0;
+          sh += use ? (over ? o[u].y : (int64_t)x[u].y) : 0;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < PMAX; ++t) {
+        acc_lo[t] = t == pr ? sl : acc_lo[t];
+        acc_hi[t] = t == pr ? sh : acc_hi[t];
       }
     }
   }
