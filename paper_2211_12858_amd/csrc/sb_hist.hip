@@ -901,20 +901,20 @@ struct ScoreOut {
 
 // RQ threads per bin: each sums its share of the node's row groups, and the
 // shares meet in LDS (integers, so the order does not matter).  The first
-// 256 threads then carry the bin through the rest.  RQ = 4 where a node
+// BT threads (64, 128 or 256: one per bin) then carry the bin through the rest.  RQ = 4 where a node
 // spans many row groups (the first levels), else 1.  The scan over bins runs
 // in registers (DPP inside each wave, wave totals through LDS), so a block
 // holds under 1 KB of LDS past the quarters' sums and the deep levels, with
 // thousands of blocks, are limited by registers: 4 to 6 blocks per CU.
-template <int PMAX, int RQ>
-__global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, ScoreOut so) {
+template <int PMAX, int RQ, int BT>
+__global__ void __launch_bounds__(BT * RQ) k_hist_reduce_score(HistArgs a, ScoreOut so) {
   const int f = blockIdx.x, p = blockIdx.y;
   const int32_t j = node_of(a, p);
   if (j < 0 || j >= a.n_nodes || f >= a.m) return;
   const int B = a.n_bins, c = a.c, k = c - 1;
   const int s = f / a.f, fl = f - s * a.f;
   const int FB = a.f * B;
-  const int bin = threadIdx.x & 255, quarter = threadIdx.x >> 8;
+  const int bin = threadIdx.x % BT, quarter = threadIdx.x / BT;
   const bool on = bin < B;
   const bool sib = a.Hp && (j == 2 * p || j == 2 * p + 1);
   const int64_t cpn = (int64_t)a.m * c * B;
@@ -1011,10 +1011,10 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
   }
   // the quarters meet: quarters 1..3 leave their sums in LDS, quarter 0
   // adds them
-  extern __shared__ longlong2 part[];  // [quarter - 1][pair][256]
+  extern __shared__ longlong2 part[];  // [quarter - 1][pair][BT]
   if (RQ > 1 && quarter > 0) {
 #pragma unroll
-    for (int pr = 0; pr < PMAX; ++pr) part[((quarter - 1) * PMAX + pr) * 256 + bin] = make_longlong2(acc_lo[pr], acc_hi[pr]);
+    for (int pr = 0; pr < PMAX; ++pr) part[((quarter - 1) * PMAX + pr) * BT + bin] = make_longlong2(acc_lo[pr], acc_hi[pr]);
   }
   if (RQ > 1) __syncthreads();
   if (RQ > 1 && quarter == 0) {
@@ -1022,14 +1022,14 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
     for (int qq = 0; qq < RQ - 1; ++qq)
 #pragma unroll
       for (int pr = 0; pr < PMAX; ++pr) {
-        const longlong2 v = part[(qq * PMAX + pr) * 256 + bin];
+        const longlong2 v = part[(qq * PMAX + pr) * BT + bin];
         acc_lo[pr] += v.x;
         acc_hi[pr] += v.y;
       }
   }
   // fp64 histogram values of this bin, v[0] of the built node j and v[1] of
   // its sibling (by subtraction), written to H and kept in registers for the
-  // scan: the bins are the block's first 256 threads, so the prefix over
+  // scan: the bins are the block's first BT threads, so the prefix over
   // bins is a prefix over lanes, then over the block's first waves
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nw = (B + 63) >> 6;  // waves that hold bins
@@ -1054,9 +1054,10 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
   // magnitude (a node's channel sum is at most 2^31 rows of 2^QBITS), so
   // fp64 sums of them are exact and any order of the scan gives the same
   // bits.  Wave totals meet in LDS as [node][channel][wave].
-  __shared__ double wtot[2][2 * PMAX][4];
-  __shared__ double wbest_s[2][4];
-  __shared__ int32_t wbest_b[2][4];
+  constexpr int BW = BT / 64;
+  __shared__ double wtot[2][2 * PMAX][BW];
+  __shared__ double wbest_s[2][BW];
+  __shared__ int32_t wbest_b[2][BW];
   const int nodes = sib ? 2 : 1;
   if (scan_wave) {
 #pragma unroll
@@ -1087,7 +1088,7 @@ __global__ void __launch_bounds__(256 * RQ) k_hist_reduce_score(HistArgs a, Scor
           if (t < c) {
             double before = 0.0, tot = 0.0;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
+            for (int w = 0; w < BW; ++w) {
               const double x = wtot[u][t][w];
               tot += x;
               before += w < wave ? x : 0.0;
@@ -1236,21 +1237,30 @@ int32_t launch_build_histograms(const uint32_t* bins4, int64_t ld4, const uint8_
   if (feat_s) {
     ScoreOut so{feat_s, feat_b, lam, mcw};
     const dim3 g(m, n_build);
-    // dynamic LDS: the partial sums of quarters 1..3 ([quarter][pair][256])
+    // dynamic LDS: the partial sums of quarters 1..3 ([quarter][pair][BT])
     const int pm = pl.pairs <= 3 ? 3 : pl.pairs <= 4 ? 4 : pl.pairs <= 6 ? 6 : pl.pairs <= 8 ? 8 : 12;
     // four threads per bin where a node spans about q / n_build >= 12 row
     // groups; not at 12 pairs, where the 1024-thread block would spill
     const bool wide = pl.q >= 12 * n_build && pm < 12;
-    const int rq = wide ? 4 : 1;
-    const size_t lds = (size_t)(rq - 1) * pm * 256 * 16;
-#define SB_RS(P, R) hipLaunchKernelGGL((k_hist_reduce_score<P, R>), g, dim3(256 * R), lds, st, a, so)
+    // as many threads per quarter as there are bins, in whole waves: with 256
+    // throughout, 192 of them were idle at 64 bins
+    const int bt = n_bins <= 64 ? 64 : n_bins <= 128 ? 128 : 256;
+    auto launch = [&](auto kernel, int rq) {
+      hipLaunchKernelGGL(kernel, g, dim3(bt * rq), (size_t)(rq - 1) * pm * bt * 16, st, a, so);
+    };
+#define SB_RS(P, R)                                             \
+  do {                                                          \
+    if (bt == 64) launch(k_hist_reduce_score<P, R, 64>, R);     \
+    else if (bt == 128) launch(k_hist_reduce_score<P, R, 128>, R); \
+    else launch(k_hist_reduce_score<P, R, 256>, R);             \
+  } while (0)
     if (pm == 3) { if (wide) SB_RS(3, 4); else SB_RS(3, 1); }
     else if (pm == 4) { if (wide) SB_RS(4, 4); else SB_RS(4, 1); }
     else if (pm == 6) { if (wide) SB_RS(6, 4); else SB_RS(6, 1); }
     else if (pm == 8) { if (wide) SB_RS(8, 4); else SB_RS(8, 1); }
     else if (pl.pairs <= 12) SB_RS(12, 1);
-#undef SB_RS
     else return fail(SB_E_UNSUPPORTED, "sb_grow_tree: the fused histogram scoring takes at most 24 channels");
+#undef SB_RS
   } else {
     dim3 rg((pl.cells + 255) / 256, n_build, pl.slices);
     hipLaunchKernelGGL(k_hist_reduce, rg, dim3(256), 0, st, a);
