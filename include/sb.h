@@ -466,9 +466,9 @@ int32_t sb_update_predictions(float* F, int64_t n, int32_t d, int64_t ld_f, cons
  * sb_gradients(loss, F, ...): F is updated in place, and G, hess, h_row and
  * norm2 are those of the updated F.  Every argument means what it means in
  * those two calls, with the same ranges and errors.
- * For the softmax loss with d <= 104 and at most 256 leaves whose lr * V
- * table (n_leaves x (d | 1) doubles) fits 64 KB, the two run as one pass
- * that reads F once; otherwise as the two calls.
+ * With at most 256 leaves, the sigmoid loss, and the softmax loss with d <= 104
+ * whose lr * V table (n_leaves x (d | 1) doubles) fits 64 KB, run as one pass
+ * that reads F once; otherwise the two calls run.
  * Workspace: sb_workspace_bytes(SB_CALL_UPDATE_AND_GRADIENTS, n, d).
  */
 int32_t sb_update_and_gradients(int32_t loss, float* F, int64_t n, int32_t d, int64_t ld_f, const int32_t* row_idx,

@@ -67,6 +67,7 @@ constexpr int UPD_THREADS = 256;
 constexpr int UPD_LDS_DOUBLES = 8192;  // lr * V of one column chunk: at most 64 KB
 constexpr int UPD_JC = 16;             // columns per chunk at most
 constexpr int UPD_MAX_BLOCKS = 2048;
+constexpr int UPD_SIG_BLOCKS = 768;  // three blocks per CU; a divisor of GRAD_PARTS
 
 struct GradArgs {
   int loss;
@@ -106,6 +107,33 @@ __device__ inline void lds_sync() {
   __builtin_amdgcn_s_waitcnt(0xc07f);
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+
+// The squared norms of a tile's chunk of 16 columns from j0, staged in gbuf:
+// 16 threads per column add 16 rows each, and the column's sum goes to its
+// tile's slot.
+__device__ inline void add_norms(const GradArgs& a, float (*gbuf)[GRAD_THREADS], int64_t base, int d, int j0) {
+  if (!a.npart) return;
+  lds_sync();
+  // lanes c*16 .. c*16+15 share column c
+  const int c = threadIdx.x >> 4, seg = threadIdx.x & 15;
+  const float4* src = reinterpret_cast<const float4*>(&gbuf[c][seg * 16]);
+  double acc = 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 v = src[q];
+    acc += (double)v.x * v.x;
+    acc += (double)v.y * v.y;
+    acc += (double)v.z * v.z;
+    acc += (double)v.w * v.w;
+  }
+  acc = row16_sum(acc);  // in the row's last lane
+  if (seg == 15 && j0 + c < d) {
+    const int tile = (int)(base / GRAD_THREADS);
+    double* pp = a.npart + (int64_t)(j0 + c) * a.n_parts + tile % a.n_parts;
+    *pp = tile < a.n_parts ? acc : *pp + acc;  // the slot's first tile writes it
+  }
+  lds_sync();
 }
 
 // One tile of k_grad (the loss, whether the tile is full and whether the
@@ -165,7 +193,7 @@ __device__ inline void grad_tile(const GradArgs& a, float (*gbuf)[GRAD_THREADS],
         // e = exp(-|a|) never overflows, so s keeps its relative accuracy
         // for scores far below zero (down to fp32's subnormals)
         const float e = expf(-fabsf(x[u]));
-        const float sg = x[u] >= 0.0f ? 1.0f / (1.0f + e) : e / (1.0f + e);
+        const float sg = (x[u] >= 0.0f ? 1.0f : e) / (1.0f + e);
         g = sg - (float)yb[u];
         hh = sg * (1.0f - sg);
       }
@@ -176,28 +204,7 @@ __device__ inline void grad_tile(const GradArgs& a, float (*gbuf)[GRAD_THREADS],
       hsum += (j < d) ? hh : 0.0f;
       gbuf[u][tid] = ok ? g : 0.0f;
     }
-    if (a.npart) {
-      lds_sync();
-      // 16 threads per column, 16 rows each; lanes c*16 .. c*16+15 share column c
-      const int c = tid >> 4, seg = tid & 15;
-      const float4* src = reinterpret_cast<const float4*>(&gbuf[c][seg * 16]);
-      double acc = 0.0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 v = src[q];
-        acc += (double)v.x * v.x;
-        acc += (double)v.y * v.y;
-        acc += (double)v.z * v.z;
-        acc += (double)v.w * v.w;
-      }
-      acc = row16_sum(acc);  // in the row's last lane
-      if (seg == 15 && j0 + c < d) {
-        const int tile = (int)(base / GRAD_THREADS);
-        double* pp = a.npart + (int64_t)(j0 + c) * a.n_parts + tile % a.n_parts;
-        *pp = tile < a.n_parts ? acc : *pp + acc;  // the slot's first tile writes it
-      }
-      lds_sync();
-    }
+    add_norms(a, gbuf, base, d, j0);
   }
   if (a.h_row && ok) a.h_row[row] = hsum * (1.0f / (float)d);
 }
@@ -216,6 +223,102 @@ __global__ void __launch_bounds__(GRAD_THREADS) k_grad(GradArgs a) {
     } else {
       if (full) grad_tile<LOSS, true, false>(a, gbuf, base, d);
       else grad_tile<LOSS, false, false>(a, gbuf, base, d);
+    }
+  }
+}
+
+// The sigmoid loss at the updated scores, one pass: the update of the previous
+// tree (as k_update) and the derivatives (as k_grad) of a chunk of 16 columns
+// for every tile of the block, then the next chunk, so that lr * V of the
+// chunk is staged in LDS once per block (leaf-major with an odd stride).  F is
+// read once: 300,001 rows x 203 outputs, 128 leaves, 273 us for k_update and
+// k_grad, 228 us here.  The row sums of the hessians wait in h_row between the
+// chunks (fp32, as in k_grad's register).
+template <bool FULL, bool HESS>
+__device__ inline void update_sigmoid_tile(const GradArgs& a, float (*gbuf)[GRAD_THREADS], const double* lv,
+                                           int64_t base, int d, int j0) {
+  const int tid = threadIdx.x;
+  const int64_t row = base + tid;
+  const bool ok = FULL || row < a.n;
+  const int loc = ok ? tid : (int)(a.n - 1 - base);  // rows past the end read row n-1 and store nothing
+  // column u's offset is u leading dimensions, capped at column d-1 (columns
+  // past d, in the last chunk only, repeat it and store its own values there);
+  // the addresses are a uniform base and the lane's 32-bit offset
+  const int last = d - 1 - j0;
+  const float* Fb = a.F + (int64_t)j0 * a.ld_f + base;
+  const uint8_t* Yb = a.Y + (int64_t)j0 * a.ld_y + base;
+  float x[GRAD_JC];
+  uint8_t yb[GRAD_JC];
+#pragma unroll
+  for (int u = 0; u < GRAD_JC; ++u) {
+    x[u] = Fb[loc];
+    if (u < last) Fb += a.ld_f;
+  }
+#pragma unroll
+  for (int u = 0; u < GRAD_JC; ++u) {
+    yb[u] = Yb[loc];
+    if (u < last) Yb += a.ld_y;
+  }
+  int L = a.ids[base + loc];
+  L = L < a.n_leaves ? L : a.n_leaves - 1;
+  const double* lvL = lv + L * (GRAD_JC + 1);
+  float hsum = a.h_row && j0 > 0 ? a.h_row[base + loc] : 0.0f;
+  float* Fw = a.F_upd + (int64_t)j0 * a.ld_f + base;
+  float* Gw = a.G + (int64_t)j0 * a.ld_g + base;
+  float* Hw = HESS ? a.hess + (int64_t)j0 * a.ld_h + base : nullptr;
+#pragma unroll
+  for (int u = 0; u < GRAD_JC; ++u) {
+    const float f = (float)((double)x[u] + lvL[u]);
+    const float e = expf(-fabsf(f));
+    const float sg = (f >= 0.0f ? 1.0f : e) / (1.0f + e);
+    const float g = sg - (float)yb[u];
+    const float hh = sg * (1.0f - sg);
+    if (ok) {
+      Fw[tid] = f;
+      Gw[tid] = g;
+      if (HESS) Hw[tid] = hh;
+    }
+    if (u < last) {
+      Fw += a.ld_f;
+      Gw += a.ld_g;
+      if (HESS) Hw += a.ld_h;
+    }
+    hsum += (u <= last) ? hh : 0.0f;
+    gbuf[u][tid] = ok ? g : 0.0f;
+  }
+  add_norms(a, gbuf, base, d, j0);
+  if (a.h_row && ok) a.h_row[row] = j0 + GRAD_JC < d ? hsum : hsum * (1.0f / (float)d);
+}
+
+// The block's tiles are t0, t0 + grid, ...: blocks go to the 8 XCDs in turn,
+// and each XCD takes a run of neighbouring t0, because neighbouring tiles share
+// cache lines where columns do not start on a line (n = 300,001: 243 us
+// without, 227 us with, before; the other passes over F and G gain at some sizes and
+// lose at others).  The launch has a multiple of 8 blocks.
+__global__ void __launch_bounds__(GRAD_THREADS) k_update_sigmoid(GradArgs a, int grid) {
+  __shared__ __align__(16) float gbuf[GRAD_JC][GRAD_THREADS];
+  extern __shared__ double lv[];  // lr * V of the chunk, [leaf][GRAD_JC + 1]
+  const int t0 = (int)(blockIdx.x & 7) * ((grid + 7) >> 3) + (int)(blockIdx.x >> 3);
+  if (t0 >= grid) return;
+  for (int j0 = 0; j0 < a.d; j0 += GRAD_JC) {
+    __syncthreads();  // the previous chunk's readers are done
+    for (int e = threadIdx.x; e < a.n_leaves * GRAD_JC; e += GRAD_THREADS) {
+      const int L = e / GRAD_JC, u = e % GRAD_JC;
+      lv[L * (GRAD_JC + 1) + u] = a.lr * a.V[(int64_t)L * a.ld_v + (j0 + u < a.d ? j0 + u : a.d - 1)];
+    }
+    __syncthreads();
+    for (int tile = t0; tile < a.n_tiles; tile += grid) {
+      int d = a.d;
+      asm volatile("" : "+s"(d));
+      const int64_t base = (int64_t)tile * GRAD_THREADS;
+      const bool full = base + GRAD_THREADS <= a.n;
+      if (a.hess) {
+        if (full) update_sigmoid_tile<true, true>(a, gbuf, lv, base, d, j0);
+        else update_sigmoid_tile<false, true>(a, gbuf, lv, base, d, j0);
+      } else {
+        if (full) update_sigmoid_tile<true, false>(a, gbuf, lv, base, d, j0);
+        else update_sigmoid_tile<false, false>(a, gbuf, lv, base, d, j0);
+      }
     }
   }
 }
@@ -296,27 +399,7 @@ __device__ inline void grad_softmax_tile(const GradArgs& a, float (*gbuf)[GRAD_T
       hsum += (j < d) ? hh : 0.0f;
       gbuf[u][tid] = ok ? g : 0.0f;
     }
-    if (a.npart) {
-      lds_sync();
-      const int c = tid >> 4, seg = tid & 15;
-      const float4* src = reinterpret_cast<const float4*>(&gbuf[c][seg * 16]);
-      double acc = 0.0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 v = src[q];
-        acc += (double)v.x * v.x;
-        acc += (double)v.y * v.y;
-        acc += (double)v.z * v.z;
-        acc += (double)v.w * v.w;
-      }
-      acc = row16_sum(acc);  // in the row's last lane
-      if (seg == 15 && j0 + c < d) {
-        const int tile = (int)(base / GRAD_THREADS);
-        double* pp = a.npart + (int64_t)(j0 + c) * a.n_parts + tile % a.n_parts;
-        *pp = tile < a.n_parts ? acc : *pp + acc;  // the slot's first tile writes it
-      }
-      lds_sync();
-    }
+    add_norms(a, gbuf, base, d, j0);
   }
   if (a.h_row && ok) a.h_row[row] = hsum * (1.0f / (float)d);
 }
@@ -524,7 +607,9 @@ int32_t launch_update_gradients(int32_t loss, float* F, int64_t n, int32_t d, in
   void* ws_ids = w + grad_ws_bytes(n, d);
   const int stride = d | 1;  // odd: lanes of different leaves fall on different banks
   const int64_t table = (int64_t)n_leaves * stride * 8;
-  if (!(loss == SB_LOSS_SOFTMAX_CE && d <= 104 && n_leaves <= 256 && table <= UPDGRAD_LDS_BYTES)) {
+  const bool softmax_fused = loss == SB_LOSS_SOFTMAX_CE && d <= 104 && table <= UPDGRAD_LDS_BYTES;
+  const size_t chunk_table = (size_t)n_leaves * (GRAD_JC + 1) * 8;  // at most 34 KB
+  if (n_leaves > 256 || !(softmax_fused || loss == SB_LOSS_SIGMOID_BCE)) {
     const int32_t rc = launch_update(F, n, d, ld_f, row_idx, leaf_off, n_leaves, V, ld_v, lr, ws_ids, st);
     if (rc) return rc;
     return launch_gradients(loss, F, n, d, ld_f, labels, Y, ld_y, G, ld_g, hess, ld_hess, h_row, norm2, ws, st);
@@ -541,7 +626,15 @@ int32_t launch_update_gradients(int32_t loss, float* F, int64_t n, int32_t d, in
   a.V = V;
   a.ld_v = ld_v;
   a.lr = lr;
-  launch_softmax_regs<true>(a, (size_t)table, st);
+  if (loss == SB_LOSS_SIGMOID_BCE) {
+    // the chunk's table is staged by every block: up to two tiles per block
+    // where one each would give more blocks than run at once
+    const int per = (int)((tiles + UPD_SIG_BLOCKS - 1) / UPD_SIG_BLOCKS);
+    const int grid = tiles <= GRAD_PARTS ? (int)((tiles + per - 1) / per) : grad_grid(tiles, UPD_SIG_BLOCKS);
+    hipLaunchKernelGGL(k_update_sigmoid, dim3((grid + 7) / 8 * 8), dim3(GRAD_THREADS), chunk_table, st, a, grid);
+  } else {
+    launch_softmax_regs<true>(a, (size_t)table, st);
+  }
   if (norm2) hipLaunchKernelGGL(k_grad_norm_final, dim3((d + 3) / 4), dim3(256), 0, st, npart, d, parts, norm2);
   return check_launch("sb_update_and_gradients");
 }
