@@ -5,7 +5,8 @@
 // k_grad: one thread per row, the rows of a block in one 256-row tile, tiles
 //   grid-strided.  The lanes of a wave take consecutive rows, so every load
 //   and store is one 256-byte run of a column of the column-major matrices.
-//   Softmax cross-entropy: a first pass over the row's scores keeps a running
+//   Softmax cross-entropy (rows of more than 1024 scores; narrower ones stay in
+//   registers, k_grad_softmax_regs and k_grad_softmax_wide): a first pass over the row's scores keeps a running
 //   maximum and the sum of exp(a - max), rescaled chunk by chunk; the second
 //   pass re-reads the scores and writes g = p - onehot(y), h = p (1 - p).
 //   Sigmoid cross-entropy needs one pass: g = s - Y, h = s (1 - s).
@@ -434,6 +435,213 @@ __global__ void __launch_bounds__(GRAD_THREADS) k_grad_softmax_regs(GradArgs a) 
   }
 }
 
+// Softmax cross-entropy of wide rows (104 < d <= 1024): the scores of ROWS rows
+// stay in the registers of one block, WIDE_C = 32 columns per lane, so F is
+// read once (the two-pass kernel above reads it twice: 700,001 x 200 399 us, 290 us
+// here; 300,007 x 1000 854 us, 703 us here).  Up to 512 columns a wave takes 64
+// rows x 32 columns; past that 32 rows x 64 columns, its upper 32 lanes the
+// second 32 columns, so that 16 waves reach 1024 (64 columns per lane need more
+// than the 128 registers that 16 waves have: spilled, 1722 us).  The waves'
+// maxima and sums of exp(a - max) meet in LDS (two barriers per tile that wait
+// for LDS operations only).  While a tile's gradients go out, column by column,
+// the same register takes the column's score of the block's next tile, so the
+// loads are in flight across the barriers and the stores.
+//
+// Column norms: the squares of columns c and c + 16 meet by exchanging rows of
+// 16 lanes (v_permlane16_swap: a lane ends with two rows' squares of one of the
+// two columns), and the 16 fp64 sums of a tile by exchanging half of the
+// remaining columns with the partner lane (DPP mirrors and quad permutations),
+// so lane l ends with column l mod 32's sum over its rows, in a fixed order, and
+// adds it to its own fp64 total over the block's tiles.  Block b's totals are
+// partial b.
+template <int CTRL>
+__device__ inline double dpp_double(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+// v[0..N): the lane keeps the half of the columns that its bit names, adds the
+// partner's values of them and passes the other half on.
+template <int CTRL, int N>
+__device__ inline void exchange_half(double (&v)[16], bool upper) {
+#pragma unroll
+  for (int c = 0; c < N / 2; ++c) {
+    const double keep = upper ? v[c + N / 2] : v[c];
+    const double send = upper ? v[c] : v[c + N / 2];
+    v[c] = keep + dpp_double<CTRL>(send);
+  }
+}
+__device__ inline void swap_rows(float& x, float& y) {  // x's odd rows of 16 lanes <-> y's even rows
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+
+constexpr int WIDE_C = 32;  // columns per lane
+constexpr int WIDE_MAX_WAVES = 16;
+constexpr int WIDE_MAX_D = 64 * WIDE_MAX_WAVES;
+// lane offsets within a wave's columns are 32-bit byte offsets
+constexpr int64_t WIDE_MAX_LD = int64_t(1) << 24;
+
+__device__ inline float load_at(const float* base, uint32_t bytes) {
+  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + bytes);
+}
+__device__ inline void store_at(float* base, uint32_t bytes, float v) {
+  *reinterpret_cast<float*>(reinterpret_cast<char*>(base) + bytes) = v;
+}
+
+// FULLC: all columns of the wave exist; else those past d - 1 load column d - 1
+// and are dropped.
+template <int ROWS, bool FULLC, bool HESS>
+__device__ __forceinline__ void softmax_wide_wave(const GradArgs& a, float (*sred)[WIDE_MAX_WAVES][64], int nw, int w,
+                                                  int bx, int grid, int tiles) {
+  constexpr int PARTS = 64 / ROWS;  // lanes of a row
+  const uint32_t lane = threadIdx.x & 63, rl = lane & (ROWS - 1);
+  const int hb = PARTS == 1 ? 0 : (int)(lane >> 5);
+  const int j0 = w * WIDE_C * PARTS, c0 = hb * WIDE_C;  // the wave's first column, the lane's first from there
+  const int last = a.d - 1 - j0;                        // the wave's last column, from j0
+  // A column's address is a uniform base that steps by the leading dimension
+  // and the lane's byte offset: its row and, for the upper half, 32 columns.
+  // Where those columns do not all exist the offset of slot i is capped at the
+  // wave's last column (uniform bases alone serve one column set per wave).
+  constexpr bool STEP = FULLC || PARTS == 1;
+  auto at = [&](int i, int cl, uint32_t row, int64_t ld) -> uint32_t {
+    if (PARTS == 1) return 4 * row;
+    if (FULLC) return 4 * (row + (uint32_t)cl * (uint32_t)ld);
+    const int c = cl + i < last ? cl + i : last;
+    return 4 * (row + (uint32_t)c * (uint32_t)ld);
+  };
+  auto rows_of = [&](int tile, int64_t& base, uint32_t& loc) {
+    base = (int64_t)tile * ROWS;
+    const int64_t left = a.n - 1 - base;  // rows past the end read row n-1
+    loc = rl < left ? rl : (uint32_t)left;
+  };
+  int64_t base;
+  uint32_t loc;
+  rows_of(bx, base, loc);
+  int y = a.labels[base + loc] - j0 - c0;
+  float x[WIDE_C];
+  {
+    const float* p = a.F + (int64_t)j0 * a.ld_f + base;
+#pragma unroll
+    for (int i = 0; i < WIDE_C; ++i) {
+      x[i] = load_at(p, at(i, c0, loc, a.ld_f));
+      if (STEP && (FULLC || i < last)) p += a.ld_f;
+    }
+  }
+  double total = 0.0;
+  for (int tile = bx; tile < tiles; tile += grid) {
+    const bool ok = base + rl < a.n;
+    float m4[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+    for (int i = 4; i < WIDE_C; ++i) m4[i & 3] = fmaxf(m4[i & 3], x[i]);
+    float m = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
+    sred[0][w][lane] = m;
+    lds_sync();
+    for (int u = 0; u < nw; ++u)
+#pragma unroll
+      for (int h = 0; h < PARTS; ++h) m = fmaxf(m, sred[0][u][ROWS * h + rl]);
+    // x[i] becomes exp(x[i] - max), reused for p below
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < WIDE_C; ++i) {
+      x[i] = expf(x[i] - m);
+      s += (FULLC || c0 + i <= last) ? x[i] : 0.0f;
+    }
+    sred[1][w][lane] = s;
+    lds_sync();
+    s = 0.0f;
+    for (int u = 0; u < nw; ++u)
+#pragma unroll
+      for (int h = 0; h < PARTS; ++h) s += sred[1][u][ROWS * h + rl];
+    const float inv = 1.0f / s;
+    float hsum = 0.0f;
+    // the next tile (past the last: this one again, not used)
+    int64_t nbase;
+    uint32_t nloc;
+    rows_of(tile + grid < tiles ? tile + grid : tile, nbase, nloc);
+    const int ny = a.labels[nbase + nloc] - j0 - c0;
+    // the columns' addresses step by the leading dimensions, which the compiler
+    // sees anew at every step: it would otherwise form all column offsets
+    // before the tile loop and hold them, spilled, across it
+    int64_t ld_f = a.ld_f, ld_g = a.ld_g, ld_h = a.ld_h;
+    const float* Fc[2];
+    float *Gc[2], *Hc[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int jq = j0 + (!STEP ? 0 : FULLC || 16 * q < last ? 16 * q : last);
+      Fc[q] = a.F + (int64_t)jq * ld_f + nbase;
+      Gc[q] = a.G + (int64_t)jq * ld_g + base;
+      Hc[q] = HESS ? a.hess + (int64_t)jq * ld_h + base : nullptr;
+    }
+    double v[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      float g2[2];
+      asm volatile("" : "+s"(ld_f), "+s"(ld_g));
+      if (HESS) asm volatile("" : "+s"(ld_h));
+      int cl = c0;  // as the leading dimensions
+      if (!STEP) asm volatile("" : "+v"(cl));
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int i = c + 16 * q;
+        const bool live = ok && (FULLC || cl + i <= last);
+        const float p = x[i] * inv;
+        const float g = i == y ? p - 1.0f : p;
+        const float hh = p * (1.0f - p);
+        if (live) {
+          store_at(Gc[q], at(i, cl, rl, ld_g), g);
+          if (HESS) store_at(Hc[q], at(i, cl, rl, ld_h), hh);
+          hsum += hh;
+        }
+        g2[q] = live ? g : 0.0f;
+        x[i] = load_at(Fc[q], at(i, cl, nloc, ld_f));
+        if (STEP && (FULLC || i < last)) {
+          Fc[q] += ld_f;
+          Gc[q] += ld_g;
+          if (HESS) Hc[q] += ld_h;
+        }
+      }
+      swap_rows(g2[0], g2[1]);
+      v[c] = (double)g2[0] * g2[0] + (double)g2[1] * g2[1];
+    }
+    exchange_half<0x140, 16>(v, lane & 8);  // row_mirror: the partner differs in bit 3 (and below)
+    exchange_half<0x141, 8>(v, lane & 4);   // row_half_mirror: in bit 2 (and below)
+    exchange_half<0x4e, 4>(v, lane & 2);    // quad_perm [2, 3, 0, 1]
+    exchange_half<0xb1, 2>(v, lane & 1);    // quad_perm [1, 0, 3, 2]
+    total += v[0];
+    if (a.h_row) {
+      sred[2][w][lane] = hsum;
+      lds_sync();
+      if (w == 0 && hb == 0 && ok) {
+        float hs = 0.0f;
+        for (int u = 0; u < nw; ++u)
+#pragma unroll
+          for (int h = 0; h < PARTS; ++h) hs += sred[2][u][ROWS * h + rl];
+        a.h_row[base + rl] = hs * (1.0f / (float)a.d);
+      }
+    }
+    base = nbase;
+    loc = nloc;
+    y = ny;
+  }
+  if constexpr (PARTS == 1) total += __shfl_xor(total, 32, 64);  // the rows of the other half
+  const int col = j0 + (int)(PARTS == 1 ? (lane & 31) : lane);
+  if (a.npart && lane < 32 * PARTS && col < a.d) a.npart[(int64_t)col * a.n_parts + bx] = total;
+}
+
+template <int ROWS, bool HESS>
+__global__ void __launch_bounds__(64 * WIDE_MAX_WAVES) k_grad_softmax_wide(GradArgs a, int grid, int tiles) {
+  __shared__ float sred[3][WIDE_MAX_WAVES][64];
+  // each XCD takes a run of neighbouring tiles (see k_update_sigmoid)
+  const int bx = (int)(blockIdx.x & 7) * ((grid + 7) >> 3) + (int)(blockIdx.x >> 3);
+  if (bx >= grid) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  constexpr int WC = WIDE_C * (64 / ROWS);
+  if ((w + 1) * WC <= a.d) softmax_wide_wave<ROWS, true, HESS>(a, sred, nw, w, bx, grid, tiles);
+  else softmax_wide_wave<ROWS, false, HESS>(a, sred, nw, w, bx, grid, tiles);
+}
+
 // One wave per column: lane l adds partials l, l+64, ... in order, then a fixed butterfly.
 __global__ void __launch_bounds__(256) k_grad_norm_final(const double* __restrict__ npart, int32_t d, int32_t parts,
                                                          double* __restrict__ norm2) {
@@ -551,6 +759,34 @@ void launch_softmax_regs(const GradArgs& a, size_t lds, hipStream_t st) {
   }
 }
 
+// The register softmax kernel for 104 < d <= 1024: 64 rows x 32 columns per
+// wave (up to 16 waves) or, past 512 columns, 32 rows x 64.  As many blocks as
+// fit at once, each with the same number of tiles, and no more than the norm
+// partials' slots (GradArgs::n_parts on entry); returns the blocks, the
+// partials' stride.
+int launch_softmax_wide(GradArgs a, hipStream_t st) {
+  const int which = a.d <= WIDE_C * WIDE_MAX_WAVES ? 0 : 1, rows = which == 0 ? 64 : 32;
+  const int wc = WIDE_C * (64 / rows), threads = 64 * ((a.d + wc - 1) / wc);
+  const int tiles = (int)((a.n + rows - 1) / rows);
+  static thread_local int fit_threads[2] = {0, 0}, fit[2] = {0, 0};  // per-thread cache of the occupancy query
+  if (fit_threads[which] != threads) {
+    fit[which] = which == 0 ? resident_blocks(k_grad_softmax_wide<64, false>, threads)
+                            : resident_blocks(k_grad_softmax_wide<32, false>, threads);
+    fit_threads[which] = threads;
+  }
+  int most = fit[which] < a.n_parts ? fit[which] : a.n_parts;
+  if (most > tiles) most = tiles;
+  const int per = (tiles + most - 1) / most, grid = (tiles + per - 1) / per;
+  a.n_parts = grid;
+  const dim3 blocks((grid + 7) / 8 * 8);
+#define SB_WIDE(R, H) hipLaunchKernelGGL((k_grad_softmax_wide<R, H>), blocks, dim3(threads), 0, st, a, grid, tiles)
+  if (which == 0) { if (a.hess) SB_WIDE(64, true); else SB_WIDE(64, false); }
+  else if (a.hess) SB_WIDE(32, true);
+  else SB_WIDE(32, false);
+#undef SB_WIDE
+  return grid;
+}
+
 }  // namespace
 
 int64_t grad_ws_bytes(int64_t n, int32_t d) {
@@ -568,11 +804,14 @@ int32_t launch_gradients(int32_t loss, const float* F, int64_t n, int32_t d, int
   const int blocks = grad_grid(tiles, GRAD_PARTS);
   if (loss == SB_LOSS_SOFTMAX_CE && d <= 104)
     launch_softmax_regs<false>(a, 0, st);
+  else if (loss == SB_LOSS_SOFTMAX_CE && d <= WIDE_MAX_D && ld_f < WIDE_MAX_LD && ld_g < WIDE_MAX_LD &&
+           (!hess || ld_hess < WIDE_MAX_LD))
+    a.n_parts = launch_softmax_wide(a, st);
   else if (loss == SB_LOSS_SOFTMAX_CE)
     hipLaunchKernelGGL(k_grad<SB_LOSS_SOFTMAX_CE>, dim3(blocks), dim3(GRAD_THREADS), 0, st, a);
   else
     hipLaunchKernelGGL(k_grad<SB_LOSS_SIGMOID_BCE>, dim3(blocks), dim3(GRAD_THREADS), 0, st, a);
-  if (norm2) hipLaunchKernelGGL(k_grad_norm_final, dim3((d + 3) / 4), dim3(256), 0, st, npart, d, parts, norm2);
+  if (norm2) hipLaunchKernelGGL(k_grad_norm_final, dim3((d + 3) / 4), dim3(256), 0, st, npart, d, a.n_parts, norm2);
   return check_launch("sb_gradients");
 }
 
