@@ -260,7 +260,8 @@ constexpr int PACK_CG = 16;                            // floats of a row writte
 // blockmax[b*(k+1) + t], reduced afterwards by k_qexp (no atomics), so the
 // workspace holds SKETCH_MAX_BLOCKS rows of maxima.  The streaming kernels
 // loop over rows in at most SKETCH_GRID_BLOCKS blocks; the matrix-core
-// projection takes one block per 512-row tile up to SKETCH_MAX_BLOCKS.
+// projection takes one block per tile of 512 or 2048 rows up to
+// SKETCH_MAX_BLOCKS.
 constexpr int SKETCH_MAX_BLOCKS = 4096;
 constexpr int SKETCH_GRID_BLOCKS = 2048;
 
@@ -617,100 +618,122 @@ k_project_sparse(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, co
 }
 
 // Dense projection on the matrix cores with v_mfma_f32_4x4x1f32, whose 16
-// blocks of 4 x 4 x 1 are here 16 groups of 4 consecutive rows of G sharing
-// one column j: one instruction multiplies 64 rows of column j by row j of
-// Pi for 4 sketch columns, so k columns take ceil(k / 4) instructions and
-// nothing is padded past a multiple of 4 (the 32 x 32 tile pads 20 columns
-// to 32).  It runs at the same flops per clock as the 32 x 32 x 2 form, and
-// MI355X's fp32 MFMA rate is twice its fp32 vector rate without packed
-// instructions, so at k >= 8 the product stops being bound by the VALU.
-// A wave computes M4_MT * 64 rows x 4 * NG sketch columns.  Operands:
-//   A (block b, 4 x 1): lane l holds G[row0 + l, j] (64 consecutive rows of
-//     one column: two 128-byte lines);
+// blocks of 4 x 4 x 1 are here 16 groups of 4 rows of G sharing one column j:
+// one instruction multiplies 64 rows of column j by row j of Pi for 4 sketch
+// columns, so k columns take ceil(k / 4) instructions and nothing is padded
+// past a multiple of 4 (the 32 x 32 tile pads 20 columns to 32).  It runs at the
+// same flops per clock as the 32 x 32 x 2 form, and MI355X's fp32 MFMA rate is
+// twice its fp32 vector rate without packed instructions, so at k >= 8 the
+// product stops being bound by the VALU.
+// A wave computes 64 M4_MT rows x 4 * NG sketch columns; lane l loads the M4_MT
+// consecutive rows M4_MT l + e of a column in one load, and component
+// e of all lanes is one A operand.  Operands:
+//   A (block b, 4 x 1): lane l holds G[row0 + M4_MT l + e, j];
 //   B (block b, 1 x 4): lane l holds Pi[j, t0 + 4g + l % 4], the same in
 //     every block, read from a block of Pi staged in LDS (zero past d and
 //     past the pass's kt columns: four addresses per read, a broadcast);
-//   D (block b, 4 x 4): register r of lane l holds row row0 + 4 (l / 4) + r,
-//     column t0 + 4g + l % 4.
-// M4_KU columns of G are loaded before their MFMAs.  The order in which the
+//   D (block b, 4 x 4): register r of lane l holds row
+//     row0 + M4_MT (4 (l / 4) + r) + e, column t0 + 4g + l % 4.
+// KU columns of G are loaded before their MFMAs.  The order in which the
 // hardware adds the products is its own, so the result is checked against
 // the exact product with the dot-product error bound.
-constexpr int M4_THREADS = 256;
-constexpr int M4_MT = 2;    // 64-row tiles per wave
+// Blocks of 16 waves read 8 KB runs of a column where 4 waves read 2 KB: the
+// read of G bounds the kernel, and longer runs read faster (2M x 1000 -> 20:
+// 1467 against 1590 us; 8 waves 1540; four rows per lane 1810, for want of
+// waves).  4 waves stay where 16-wave blocks (one per CU) would leave the last
+// round of blocks part-empty.
+constexpr int M4_SMALL = 256, M4_BIG = 1024;  // threads per block
+constexpr int M4_BIG_MAX_NG = 6;              // groups of 4 columns that 16 waves' 128 registers hold
+constexpr int M4_MT = 2;    // consecutive rows per lane
 constexpr int M4_JC = 256;  // columns of G per staged block of Pi
-constexpr int M4_KU = 16;   // columns of G per batch of loads
-static_assert(M4_JC % M4_KU == 0, "a batch of columns never passes the staged block");
+// columns of G per batch of loads (16 waves have 128 registers each)
+constexpr int m4_ku(int ng, int threads) { return threads == M4_BIG && ng > 5 ? 8 : 16; }
+static_assert(M4_JC % 16 == 0, "a batch of columns never passes the staged block");
 typedef float mf_v4 __attribute__((ext_vector_type(4)));
+// M4_MT consecutive values from a 4-byte aligned address, streamed
+typedef float mf_rows __attribute__((ext_vector_type(M4_MT), aligned(4)));
 
-template <int NG>
-__global__ void __launch_bounds__(M4_THREADS)
+// The products of one tile's columns [j0, j0 + jc) (Pi staged in sPi).  FULL:
+// every lane's rows exist; else a row past the end reads row n - 1 (its
+// results are not stored).
+template <int NG, int KU, bool FULL>
+__device__ __forceinline__ void project_columns(const float* __restrict__ G, int64_t ld_g, int64_t row, int64_t n,
+                                                int j0, int jc, const float* sPi, mf_v4 (&acc)[M4_MT][NG]) {
+  constexpr int W = 4 * NG;
+  const int cq = threadIdx.x & 3;  // this lane's column within each group of 4
+  for (int kk = 0; kk < jc; kk += KU) {
+    mf_rows a[KU];
+#pragma unroll
+    for (int u = 0; u < KU; ++u) {
+      // past the block: a finite value of column jc - 1 times a zero of Pi
+      const float* col = G + (int64_t)(j0 + (kk + u < jc ? kk + u : jc - 1)) * ld_g;
+      if constexpr (FULL) {
+        a[u] = __builtin_nontemporal_load(reinterpret_cast<const mf_rows*>(col + row));
+      } else {
+#pragma unroll
+        for (int e = 0; e < M4_MT; ++e) a[u][e] = col[row + e < n ? row + e : n - 1];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < KU; ++u) {
+      const float* pr = sPi + (kk + u) * W + cq;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const float b = pr[4 * g];
+#pragma unroll
+        for (int e = 0; e < M4_MT; ++e)
+          acc[e][g] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[u][e], b, acc[e][g], 0, 0, 0);
+      }
+    }
+  }
+}
+
+template <int NG, int THREADS>
+__global__ void __launch_bounds__(THREADS)
 k_project_mfma4(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, const float* __restrict__ Pi, int k,
                 int t0, const float* __restrict__ h, float* __restrict__ GH, int64_t ld_gh,
                 uint32_t* __restrict__ blockmax) {
   constexpr int W = 4 * NG;  // sketch columns of the pass, padded to a multiple of 4
+  constexpr int KU = m4_ku(NG, THREADS);
   __shared__ float sPi[M4_JC * W];
-  __shared__ uint32_t smax[M4_THREADS / 64][W + 1];
+  __shared__ uint32_t smax[THREADS / 64][W + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kt = (k - t0 < W) ? k - t0 : W;
   const bool last = t0 + kt >= k;
-  const int cq = lane & 3;  // this lane's column within each group of 4
+  const int cq = lane & 3;
   uint32_t mx[NG], mxh = 0u;
 #pragma unroll
   for (int g = 0; g < NG; ++g) mx[g] = 0u;
-  constexpr int64_t ROWS = (M4_THREADS / 64) * M4_MT * 64;  // rows per block per pass
+  constexpr int64_t ROWS = (THREADS / 64) * M4_MT * 64;  // rows per block per pass
   for (int64_t base = (int64_t)blockIdx.x * ROWS; base < n; base += (int64_t)gridDim.x * ROWS) {
     const int64_t rw = base + (int64_t)wave * M4_MT * 64;
-    int64_t rc[M4_MT];
-#pragma unroll
-    for (int mt = 0; mt < M4_MT; ++mt) {
-      const int64_t r = rw + mt * 64 + lane;
-      rc[mt] = r < n ? r : n - 1;  // rows past the end read row n-1 and store nothing
-    }
+    const bool full = rw + M4_MT * 64 <= n;
     mf_v4 acc[M4_MT][NG];
 #pragma unroll
-    for (int mt = 0; mt < M4_MT; ++mt)
+    for (int e = 0; e < M4_MT; ++e)
 #pragma unroll
-      for (int g = 0; g < NG; ++g) acc[mt][g] = mf_v4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int g = 0; g < NG; ++g) acc[e][g] = mf_v4{0.0f, 0.0f, 0.0f, 0.0f};
     for (int j0 = 0; j0 < d; j0 += M4_JC) {
       const int jc = (d - j0 < M4_JC) ? d - j0 : M4_JC;
       __syncthreads();  // the previous block of Pi is no longer read
-      for (int e = threadIdx.x; e < M4_JC * W; e += M4_THREADS) {
+      for (int e = threadIdx.x; e < M4_JC * W; e += THREADS) {
         const int jr = e / W, c = e - jr * W;
         sPi[e] = (jr < jc && c < kt) ? Pi[(int64_t)(j0 + jr) * k + t0 + c] : 0.0f;
       }
       __syncthreads();
-      for (int kk = 0; kk < jc; kk += M4_KU) {
-        float a[M4_KU][M4_MT];
-#pragma unroll
-        for (int u = 0; u < M4_KU; ++u) {
-          // past the block: a finite value of column jc - 1 times a zero of Pi
-          const int64_t jg = j0 + (kk + u < jc ? kk + u : jc - 1);
-#pragma unroll
-          for (int mt = 0; mt < M4_MT; ++mt) a[u][mt] = ld_stream(G + jg * ld_g + rc[mt]);
-        }
-#pragma unroll
-        for (int u = 0; u < M4_KU; ++u) {
-          const float* pr = sPi + (kk + u) * W + cq;
-#pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            const float b = pr[4 * g];
-#pragma unroll
-            for (int mt = 0; mt < M4_MT; ++mt)
-              acc[mt][g] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[u][mt], b, acc[mt][g], 0, 0, 0);
-          }
-        }
-      }
+      if (full) project_columns<NG, KU, true>(G, ld_g, rw + M4_MT * lane, n, j0, jc, sPi, acc);
+      else project_columns<NG, KU, false>(G, ld_g, rw + M4_MT * lane, n, j0, jc, sPi, acc);
     }
 #pragma unroll
-    for (int mt = 0; mt < M4_MT; ++mt)
+    for (int e = 0; e < M4_MT; ++e)
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         const int col = 4 * g + cq;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int64_t row = rw + mt * 64 + 4 * (lane >> 2) + r;
+          const int64_t row = rw + M4_MT * (4 * (lane >> 2) + r) + e;
           if (row < n && col < kt) {
-            const float v = acc[mt][g][r];
+            const float v = acc[e][g][r];
             GH[row * ld_gh + t0 + col] = v;
             const uint32_t m = __float_as_uint(v) & 0x7fffffffu;
             mx[g] = m > mx[g] ? m : mx[g];
@@ -719,8 +742,8 @@ k_project_mfma4(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, con
       }
     if (last) {
 #pragma unroll
-      for (int mt = 0; mt < M4_MT; ++mt) {
-        const int64_t row = rw + mt * 64 + lane;
+      for (int e = 0; e < M4_MT; ++e) {
+        const int64_t row = rw + e * 64 + lane;
         if (row < n) {
           const float hv = h[row];
           GH[row * ld_gh + k] = hv;
@@ -746,7 +769,7 @@ k_project_mfma4(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, con
   if (threadIdx.x <= W) {
     uint32_t r = 0u;
 #pragma unroll
-    for (int w = 0; w < M4_THREADS / 64; ++w) r = smax[w][threadIdx.x] > r ? smax[w][threadIdx.x] : r;
+    for (int w = 0; w < THREADS / 64; ++w) r = smax[w][threadIdx.x] > r ? smax[w][threadIdx.x] : r;
     if (threadIdx.x < kt) blockmax[(int64_t)blockIdx.x * (k + 1) + t0 + threadIdx.x] = r;
     if (threadIdx.x == W && last) blockmax[(int64_t)blockIdx.x * (k + 1) + k] = r;
   }
@@ -864,13 +887,21 @@ SketchWs sketch_ws_layout(int64_t n, int32_t d, int32_t k) {
 int launch_dense_projection(const float* G, int64_t n, int32_t d, int64_t ld_g, const float* h, int32_t k,
                             const float* Pi, float* GH, int64_t ld_gh, uint32_t* blockmax, hipStream_t st) {
   if (k >= PROJ_MFMA_MIN_K) {
-    const int nb = sketch_blocks(n, (M4_THREADS / 64) * M4_MT * 64, SKETCH_MAX_BLOCKS);
+    // 16-wave blocks where they fill at least 0.9 of their rounds over the CUs
+    // and a pass's columns fit their registers
+    const int64_t big = (n + M4_BIG * M4_MT - 1) / (M4_BIG * M4_MT), rounds = (big + 255) / 256;
+    const int threads = big >= rounds * 256 * 9 / 10 && k <= 4 * M4_BIG_MAX_NG ? M4_BIG : M4_SMALL;
+    const int nb = sketch_blocks(n, threads * M4_MT, SKETCH_MAX_BLOCKS);
     for (int t0 = 0; t0 < k; t0 += 32) {
       const int ng = (k - t0 < 32 ? k - t0 + 3 : 32 + 3) / 4;
-#define SB_P4(NG)                                                                                                 \
-  case NG:                                                                                                        \
-    hipLaunchKernelGGL((k_project_mfma4<NG>), dim3(nb), dim3(M4_THREADS), 0, st, G, n, d, ld_g, Pi, k, t0, h, GH, \
-                       ld_gh, blockmax);                                                                          \
+#define SB_P4(NG)                                                                                              \
+  case NG:                                                                                                     \
+    if (threads == M4_BIG)                                                                                     \
+      hipLaunchKernelGGL((k_project_mfma4<(NG <= M4_BIG_MAX_NG ? NG : 1), M4_BIG>), dim3(nb), dim3(M4_BIG), 0, st, G, n, d, ld_g, Pi, k,   \
+                         t0, h, GH, ld_gh, blockmax);                                                          \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_project_mfma4<NG, M4_SMALL>), dim3(nb), dim3(M4_SMALL), 0, st, G, n, d, ld_g, Pi,  \
+                         k, t0, h, GH, ld_gh, blockmax);                                                       \
     break;
       switch (ng) { SB_P4(1) SB_P4(2) SB_P4(3) SB_P4(4) SB_P4(5) SB_P4(6) SB_P4(7) SB_P4(8) }
 #undef SB_P4
