@@ -37,24 +37,23 @@ namespace sb {
 namespace {
 
 constexpr int LEAF_THREADS = 256;
-// Rows per thread per tile: 8 (2048-row tiles), with plain channels and
-// with the derived hessians alike (4 rows per thread, 1024-row tiles, took
-// 368 against 290 us on 2M x 100: twice the per-tile maxima and cell
-// flushes per row).
-constexpr int LEAF_SPT = 8;
-constexpr int LEAF_SPT_DERIVED = 8;
-// Quantum exponent for a tile of 256 * SPT rows: tile * 2^ql <= 2^52.
-constexpr int leaf_ql(int spt) { return spt == 8 ? 41 : (spt == 4 ? 42 : 40); }
-static_assert((int64_t)(LEAF_THREADS * 8) << leaf_ql(8) <= (int64_t(1) << 52), "tile sums must stay exact in fp64");
-static_assert((int64_t)(LEAF_THREADS * 4) << leaf_ql(4) <= (int64_t(1) << 52), "tile sums must stay exact in fp64");
-constexpr int64_t LEAF_LDS_MAX = 64 * 1024;             // integer + fp64 cells of one block
-constexpr int LEAF_TARGET_BLOCKS = 4096;                // 16 per CU
+constexpr int LEAF_SPT = 8;  // rows per thread per tile
+constexpr int LEAF_TILE = LEAF_THREADS * LEAF_SPT;
+constexpr int LEAF_QL = 41;  // quantum exponent: LEAF_TILE * 2^LEAF_QL <= 2^52
+static_assert(((int64_t)LEAF_TILE << LEAF_QL) <= (int64_t(1) << 52), "tile sums must stay exact in fp64");
+// integer + fp64 cells of one block (and one integer cell per channel and copy
+// for the rows past the end)
+constexpr int64_t LEAF_LDS_MAX = 64 * 1024 + 256;
+constexpr int LEAF_TARGET_BLOCKS = 4096;  // 16 per CU
 // channels per block (fewer for many leaves, so that the cells fit LEAF_LDS_MAX)
 constexpr int LEAF_JMAX = 4;
 // with derived hessians a block holds 4 outputs (8 channels), so the
 // per-row leaf ids and labels are read once per 4 outputs
 constexpr int LEAF_JMAX_DERIVED = 8;
-// copies of each integer cell, lane l adding to copy l mod copies
+// Copies of each integer cell, lane l adding to copy l mod copies.  (16 copies,
+// whose adds have no bank conflicts, in blocks of 512 threads took 179 against
+// 158 us at 1,000,001 x 100 with derived hessians: their LDS leaves fewer waves
+// per CU, and the adds do not bound the kernel.)
 constexpr int LEAF_MAX_COPIES = 4;
 
 struct LeafArgs {
@@ -99,69 +98,40 @@ __device__ inline long long rint_to_ll(float v, double scale) {
   return __double_as_longlong(t) - 0x4338000000000000ll;
 }
 
-template <int J, int SPT>
+// A lane's rows of a tile.  DER: how the odd channels are made (0: loaded as they
+// are; 1 softmax, 2 sigmoid: the hessian of the even channel's output, formed
+// from the gradient and the target where it is used).  With DER and J >= 2 the
+// two channels of an output come from one column of G, loaded once (c0 is a
+// multiple of J, so channel c0 + j is odd when j is).
+template <int J, int SPT, int DER>
 struct LeafTile {
-  float v[SPT][J];
-  int lf[SPT];
+  static constexpr int NV = DER != 0 && J >= 2 ? J / 2 : J;  // values loaded per row
+  float v[SPT][NV];
+  uint32_t target[SPT][DER == 2 ? NV : 1];  // the row's label, or Y of each output
+  int id[SPT];                              // leaf id as loaded
 };
 
-// DER: how the odd channels are made (0: loaded as they are; 1 softmax, 2
-// sigmoid: the hessian of the even channel's output, formed after the load).
-// With DER the two channels of an output come from one column of G, loaded
-// once.
-template <int J, int SPT, typename LT, int DER>
-__device__ inline void leaf_load(const LeafArgs& a, const float* const (&col)[J], int c0, int t, int top,
-                                 LeafTile<J, SPT>& x) {
-  // Rows past the end load row n-1 and get a negative leaf id, which drops
-  // them from the adds (they may still raise the tile maximum, which only has
-  // to bound the tile's values).  No value depends on a condition, so the
-  // compiler issues every load of the tile back to back instead of waiting
-  // for each one inside its own branch.
-  const LT* ids = static_cast<const LT*>(a.leaf_of);
-  const int64_t r0 = (int64_t)t * (LEAF_THREADS * SPT);
-#pragma unroll
-  for (int s = 0; s < SPT; ++s) {
-    const int64_t row = r0 + threadIdx.x + LEAF_THREADS * s;
-    const int64_t rc = row < a.n ? row : a.n - 1;
-    const int l = (int)ids[rc];
-    x.lf[s] = (l > top ? top : l) - (row < a.n ? 0 : 0x10000);
-#pragma unroll
-    for (int j = 0; j < J; ++j) x.v[s][j] = (DER && J >= 2 && (j & 1)) ? x.v[s][j - 1] : col[j][rc];
-  }
-  if constexpr (DER != 0) {
-    // odd channel 2o+1: the hessian of output o from g = G[i, o]:
-    // softmax p = g + [o == label], sigmoid s = g + Y[i, o]; h = p (1 - p).
-    // Applied after every load of the tile is issued.
-    float tg[SPT][J];
-#pragma unroll
-    for (int s = 0; s < SPT; ++s) {
-      const int64_t row = r0 + threadIdx.x + LEAF_THREADS * s;
-      const int64_t rc = row < a.n ? row : a.n - 1;
-      const int y = DER == 1 ? (int)a.labels[rc] : -1;
-#pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const int c = c0 + j, o = c >> 1;
-        if (J >= 2 && !(j & 1)) {
-          tg[s][j] = 0.0f;  // even channel: g itself
-        } else if constexpr (DER == 1) {
-          tg[s][j] = o == y ? 1.0f : 0.0f;
-        } else {
-          tg[s][j] = (float)a.Y[(int64_t)(o < a.d ? o : a.d - 1) * a.ld_y + rc];
-        }
-      }
-    }
-    // c0 is a multiple of J, so for J >= 2 channel c0 + j is odd when j is
-    const bool c0_odd = (c0 & 1) != 0;
-#pragma unroll
-    for (int s = 0; s < SPT; ++s)
-#pragma unroll
-      for (int j = 0; j < J; ++j) {
-        if (J >= 2 ? (j & 1) != 0 : c0_odd) {
-          const float p = x.v[s][j] + tg[s][j];
-          x.v[s][j] = p * (1.0f - p);
-        }
-      }
-  }
+// Loads one lane's row s of tile t (row-major over the lanes), value o of it.
+// Rows past the end load row n-1 (they may still raise the tile maximum, which
+// only has to bound the tile's values); no load sits behind a condition.
+template <int SPT>
+__device__ inline uint32_t leaf_row(int64_t n, int t, int s) {
+  const int64_t left = n - 1 - (int64_t)t * (LEAF_THREADS * SPT);  // the tile's last row
+  const uint32_t r = threadIdx.x + LEAF_THREADS * s;
+  return r <= left ? r : (uint32_t)left;
+}
+
+// The value of channel c0 + j of row s.
+template <int J, int SPT, int DER>
+__device__ inline float leaf_value(const LeafTile<J, SPT, DER>& x, int s, int j, int c0) {
+  if constexpr (DER == 0) return x.v[s][j];
+  const int o = J >= 2 ? j >> 1 : 0;
+  const float g = x.v[s][o];
+  if (J >= 2 && !(j & 1)) return g;
+  // softmax p = g + [o == label], sigmoid s = g + Y[i, o]; h = p (1 - p)
+  const float p = g + (DER == 1 ? ((c0 + j) >> 1 == (int)x.target[s][0] ? 1.0f : 0.0f) : (float)x.target[s][o]);
+  const float h = p * (1.0f - p);
+  return J >= 2 || (c0 & 1) ? h : g;
 }
 
 // A float moved across lanes by a DPP control (row shift or row broadcast);
@@ -187,94 +157,126 @@ __device__ inline float wave_max_nonneg(float x) {
   return x;
 }
 
-// One tile: block-wide maximum per channel, quantisation, integer adds into
-// the LDS cells, then the exact fp64 conversion into the accumulators.
-template <int J, int SPT>
-__device__ inline void leaf_tile(const LeafTile<J, SPT>& x, const bool (&live)[J], float (&wmax)[LEAF_THREADS / 64][J],
-                                 double (&sconv)[J], unsigned long long* icell, double* acc, int NL, int rsh) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cells = NL * J;
-  const int copy = lane & ((1 << rsh) - 1);
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    float mx = 0.0f;
-#pragma unroll
-    for (int s = 0; s < SPT; ++s) mx = fmaxf(mx, fabsf(x.v[s][j]));
-    mx = wave_max_nonneg(mx);
-    if (lane == 63) wmax[wave][j] = mx;
-  }
-  __syncthreads();
-  double sc[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    float M = wmax[0][j];
-#pragma unroll
-    for (int w = 1; w < LEAF_THREADS / 64; ++w) M = fmaxf(M, wmax[w][j]);
-    int E = 0;
-    if (M > 0.0f) (void)frexpf(M, &E);  // M = f * 2^E with f in [0.5, 1): every |v| < 2^E
-    sc[j] = M > 0.0f ? pow2(leaf_ql(SPT) - E) : 0.0;
-    if (tid == j) sconv[j] = M > 0.0f ? pow2(E - leaf_ql(SPT)) : 0.0;
-  }
-#pragma unroll
-  for (int s = 0; s < SPT; ++s) {
-    // a row past the end adds 0 to leaf 0
-    const bool in = x.lf[s] >= 0;
-    const int l = in ? x.lf[s] : 0;
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const long long q = rint_to_ll(x.v[s][j], sc[j]);
-      if (live[j]) atomicAdd(&icell[((j * NL + l) << rsh) + copy], (unsigned long long)(in ? q : 0ll));
-    }
-  }
-  __syncthreads();
-  // The next tile's adds (and its writes of wmax and sconv) start only after
-  // its first barrier, which every thread reaches after finishing this loop.
-  for (int cell = tid; cell < cells; cell += LEAF_THREADS) {
-    unsigned long long* cp = icell + ((int64_t)cell << rsh);
-    long long q = 0;
-    for (int r = 0; r < (1 << rsh); ++r) q += (long long)cp[r];  // exact: the copies split one tile's sum
-    if (q != 0) acc[cell] += (double)q * sconv[cell / NL];
-    for (int r = 0; r < (1 << rsh); ++r) cp[r] = 0ull;
-  }
+// Barrier that waits for LDS operations only: the next tile's loads stay in
+// flight across it.  0xc07f is s_waitcnt lgkmcnt(0) in the gfx9 encoding.
+__device__ inline void leaf_sync() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
+// One block's tiles.  Per tile: block-wide maximum per channel, quantisation,
+// integer adds into the LDS cells, then the exact fp64 conversion into the
+// accumulators.  As a row's values are added, its registers take the row's
+// values of the next tile, so those loads are in flight across the rest of the
+// adds, the conversion and the barriers (boosting iteration at 2M x 100 1580 ->
+// 1557 us, with the adds behind no branch).
 template <int J, int SPT, typename LT, int DER>
 __global__ void __launch_bounds__(LEAF_THREADS) k_leaf_accum(LeafArgs a) {
-  // Cells are channel-major ([J][n_leaves]): the lanes of one add instruction
-  // share the channel, so their addresses differ by leaf and spread over the
-  // LDS banks.  Each integer cell has 2^rsh copies side by side, lane l adding
-  // to copy l mod 2^rsh: lanes whose rows share a leaf (most lanes when few
-  // leaves are large) then mostly hit different addresses.
+  // Cells are channel-major ([J][n_leaves + 1]): the lanes of one add
+  // instruction share the channel, so their addresses differ by leaf and
+  // spread over the LDS banks.  The last leaf's cell takes the rows past the end and
+  // is never read; a channel past the last one adds into cells that are never
+  // written out: no add sits behind a branch.  Each integer cell has 2^rsh copies
+  // side by side, lane l adding to copy l mod 2^rsh: lanes whose rows share a
+  // leaf (most lanes when few leaves are large) then mostly hit different
+  // addresses.
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ float wmax[LEAF_THREADS / 64][J];
   __shared__ double sconv[J];
+  using Tile = LeafTile<J, SPT, DER>;
   const int NL = a.n_leaves;
   const int cells = NL * J;
   const int rsh = a.copies_shift;
   unsigned long long* icell = reinterpret_cast<unsigned long long*>(smem);
-  double* acc = reinterpret_cast<double*>(smem + ((size_t)cells << rsh) * 8);
-  const int tid = threadIdx.x;
+  const int icells = ((NL + 1) * J) << rsh, chan = (NL + 1) << rsh;
+  double* acc = reinterpret_cast<double*>(smem + (size_t)icells * 8);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int copy = lane & ((1 << rsh) - 1);
   const int c0 = blockIdx.x * J;
   const int split = blockIdx.y;
-
-  const float* col[J];
-  bool live[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    live[j] = c0 + j < a.nch;
-    col[j] = chan_ptr(a, live[j] ? c0 + j : c0);  // a channel past the last one reads the chunk's first
-  }
-  for (int cell = tid; cell < (cells << rsh); cell += LEAF_THREADS) icell[cell] = 0ull;
-  for (int cell = tid; cell < cells; cell += LEAF_THREADS) acc[cell] = 0.0;
   const int t0 = split * a.tiles_per_split;
   const int t1 = min(a.n_tiles, t0 + a.tiles_per_split);
-  const int top = NL - 1;
-  __syncthreads();
+  const LT* ids = static_cast<const LT*>(a.leaf_of);
+
+  const float* col[Tile::NV];
+#pragma unroll
+  for (int o = 0; o < Tile::NV; ++o) {
+    const int c = c0 + (J / Tile::NV) * o;
+    col[o] = chan_ptr(a, c < a.nch ? c : c0);  // a channel past the last one reads the chunk's first
+  }
+  // row s of tile t, all its values
+  auto load_row = [&](Tile& x, int t, int s) {
+    const int64_t r0 = (int64_t)t * (LEAF_THREADS * SPT);
+    const uint32_t r = leaf_row<SPT>(a.n, t, s);
+    x.id[s] = (int)(ids + r0)[r];
+#pragma unroll
+    for (int o = 0; o < Tile::NV; ++o) x.v[s][o] = (col[o] + r0)[r];
+    if constexpr (DER == 1) x.target[s][0] = (a.labels + r0)[r];
+    if constexpr (DER == 2) {
+#pragma unroll
+      for (int o = 0; o < Tile::NV; ++o) {
+        const int out = (c0 >> 1) + o;
+        x.target[s][o] = (a.Y + (int64_t)(out < a.d ? out : a.d - 1) * a.ld_y + r0)[r];
+      }
+    }
+  };
+  Tile x;
+  if (t0 < t1) {
+#pragma unroll
+    for (int s = 0; s < SPT; ++s) load_row(x, t0, s);
+  }
+  for (int cell = tid; cell < icells; cell += LEAF_THREADS) icell[cell] = 0ull;
+  for (int cell = tid; cell < cells; cell += LEAF_THREADS) acc[cell] = 0.0;
+  leaf_sync();
 
   for (int t = t0; t < t1; ++t) {
-    LeafTile<J, SPT> x;
-    leaf_load<J, SPT, LT, DER>(a, col, c0, t, top, x);
-    leaf_tile(x, live, wmax, sconv, icell, acc, NL, rsh);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      float mx = 0.0f;
+#pragma unroll
+      for (int s = 0; s < SPT; ++s) mx = fmaxf(mx, fabsf(leaf_value<J, SPT, DER>(x, s, j, c0)));
+      mx = wave_max_nonneg(mx);
+      if (lane == 63) wmax[wave][j] = mx;
+    }
+    leaf_sync();
+    double sc[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      float M = wmax[0][j];
+#pragma unroll
+      for (int w = 1; w < LEAF_THREADS / 64; ++w) M = fmaxf(M, wmax[w][j]);
+      int E = 0;
+      if (M > 0.0f) (void)frexpf(M, &E);  // M = f * 2^E with f in [0.5, 1): every |v| < 2^E
+      sc[j] = M > 0.0f ? pow2(LEAF_QL - E) : 0.0;
+      if (tid == j) sconv[j] = M > 0.0f ? pow2(E - LEAF_QL) : 0.0;
+    }
+    const int64_t left = a.n - 1 - (int64_t)t * (LEAF_THREADS * SPT);  // the tile's last row
+    const int nt = t + 1 < t1 ? t + 1 : t;  // past the last tile: this one again, not used
+#pragma unroll
+    for (int s = 0; s < SPT; ++s) {
+      const int id = x.id[s] < NL ? x.id[s] : NL - 1;
+      const int l = tid + LEAF_THREADS * s <= left ? id : NL;
+      unsigned long long* cell = icell + (l << rsh) + copy;
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        atomicAdd(cell + j * chan, (unsigned long long)rint_to_ll(leaf_value<J, SPT, DER>(x, s, j, c0), sc[j]));
+      load_row(x, nt, s);
+    }
+    leaf_sync();
+    // The next tile's adds (and its writes of wmax and sconv) start only after
+    // its first barrier, which every thread reaches after finishing this loop.
+    for (int cell = tid; cell < cells; cell += LEAF_THREADS) {
+      const int j = cell / NL;
+      unsigned long long* cp = icell + ((cell + j) << rsh);  // one cell more per channel than acc
+      long long q = 0;
+      // (exact: the copies split one tile's sum; neighbouring lanes start at
+      // different copies, as their cells are a whole number of copies apart)
+      for (int r = 0; r < (1 << rsh); ++r) q += (long long)cp[(r + lane) & ((1 << rsh) - 1)];
+      if (q != 0) acc[cell] += (double)q * sconv[j];
+      for (int r = 0; r < (1 << rsh); ++r) cp[(r + lane) & ((1 << rsh) - 1)] = 0ull;
+    }
   }
   __syncthreads();
   for (int cell = tid; cell < cells; cell += LEAF_THREADS) {
@@ -322,18 +324,23 @@ __global__ void __launch_bounds__(256) k_narrow_labels(const int32_t* __restrict
 }
 
 struct LeafPlan {
-  int J, spt, nch, n_chunks, n_tiles, tps, splits, rsh;
+  int J, nch, n_chunks, n_tiles, tps, splits, rsh;
   int64_t lds;
 };
 
-LeafPlan leaf_plan(int64_t n, int32_t nch, int32_t n_leaves, int jmax = LEAF_JMAX, int spt = LEAF_SPT) {
+// LDS of a block of J channels with 2^rsh copies of every integer cell (one
+// leaf more than there are, for rows past the end).
+int64_t leaf_lds(int32_t n_leaves, int J, int rsh) {
+  return (int64_t)J * ((n_leaves + 1) * (int64_t(8) << rsh) + (int64_t)n_leaves * 8);
+}
+
+LeafPlan leaf_plan(int64_t n, int32_t nch, int32_t n_leaves, int jmax = LEAF_JMAX) {
   LeafPlan p{};
-  p.spt = spt;
   p.J = jmax;
-  while (p.J > 1 && (int64_t)n_leaves * p.J * 16 > LEAF_LDS_MAX) p.J >>= 1;
+  while (p.J > 1 && leaf_lds(n_leaves, p.J, 0) > LEAF_LDS_MAX) p.J >>= 1;
   p.nch = nch;
   p.n_chunks = (nch + p.J - 1) / p.J;
-  p.n_tiles = (int)((n + LEAF_THREADS * spt - 1) / (LEAF_THREADS * spt));
+  p.n_tiles = (int)((n + LEAF_TILE - 1) / LEAF_TILE);
   int splits = (LEAF_TARGET_BLOCKS + p.n_chunks - 1) / p.n_chunks;
   if (splits < 1) splits = 1;
   if (splits > p.n_tiles) splits = p.n_tiles;
@@ -341,14 +348,13 @@ LeafPlan leaf_plan(int64_t n, int32_t nch, int32_t n_leaves, int jmax = LEAF_JMA
   p.splits = (p.n_tiles + p.tps - 1) / p.tps;
   // as many copies of the integer cells (up to LEAF_MAX_COPIES) as the LDS budget allows
   p.rsh = 0;
-  while ((1 << (p.rsh + 1)) <= LEAF_MAX_COPIES && (int64_t)n_leaves * p.J * (8 * (2 << p.rsh) + 8) <= LEAF_LDS_MAX)
-    ++p.rsh;
-  p.lds = (int64_t)n_leaves * p.J * (8 * (1 << p.rsh) + 8);
+  while ((2 << p.rsh) <= LEAF_MAX_COPIES && leaf_lds(n_leaves, p.J, p.rsh + 1) <= LEAF_LDS_MAX) ++p.rsh;
+  p.lds = leaf_lds(n_leaves, p.J, p.rsh);
   return p;
 }
 
-int64_t leaf_ws_for(int64_t n, int32_t nch, int32_t n_leaves, int jmax = LEAF_JMAX, int spt = LEAF_SPT) {
-  const LeafPlan p = leaf_plan(n, nch, n_leaves, jmax, spt);
+int64_t leaf_ws_for(int64_t n, int32_t nch, int32_t n_leaves, int jmax = LEAF_JMAX) {
+  const LeafPlan p = leaf_plan(n, nch, n_leaves, jmax);
   return leaf_ids_bytes(n) + align256((int64_t)p.splits * n_leaves * nch * 8) + align256(n * 2);
 }
 
@@ -356,9 +362,9 @@ template <int J, typename LT>
 void launch_accum(const LeafPlan& p, const LeafArgs& a, hipStream_t st) {
   const dim3 g(p.n_chunks, p.splits);
   if (a.derive == 1)
-    hipLaunchKernelGGL((k_leaf_accum<J, LEAF_SPT_DERIVED, LT, 1>), g, dim3(LEAF_THREADS), (size_t)p.lds, st, a);
+    hipLaunchKernelGGL((k_leaf_accum<J, LEAF_SPT, LT, 1>), g, dim3(LEAF_THREADS), (size_t)p.lds, st, a);
   else if (a.derive == 2)
-    hipLaunchKernelGGL((k_leaf_accum<J, LEAF_SPT_DERIVED, LT, 2>), g, dim3(LEAF_THREADS), (size_t)p.lds, st, a);
+    hipLaunchKernelGGL((k_leaf_accum<J, LEAF_SPT, LT, 2>), g, dim3(LEAF_THREADS), (size_t)p.lds, st, a);
   else
     hipLaunchKernelGGL((k_leaf_accum<J, LEAF_SPT, LT, 0>), g, dim3(LEAF_THREADS), (size_t)p.lds, st, a);
 }
@@ -383,7 +389,7 @@ int64_t leaf_ws_bytes(int64_t n, int32_t d, int32_t n_leaves) {
   int64_t b = leaf_ws_for(n, d, n_leaves);
   const int64_t b1 = leaf_ws_for(n, d + 1, n_leaves);
   const int64_t b2 = leaf_ws_for(n, 2 * d, n_leaves);
-  const int64_t b3 = leaf_ws_for(n, 2 * d, n_leaves, LEAF_JMAX_DERIVED, LEAF_SPT_DERIVED);
+  const int64_t b3 = leaf_ws_for(n, 2 * d, n_leaves, LEAF_JMAX_DERIVED);
   if (b1 > b) b = b1;
   if (b2 > b) b = b2;
   if (b3 > b) b = b3;
@@ -415,7 +421,7 @@ int32_t launch_leaf_values_from_loss(int32_t loss, const float* G, int64_t n, in
                                      const int32_t* leaf_off, int32_t n_leaves, double lambda, double* V, int64_t ld_v,
                                      void* ws, hipStream_t st) {
   const int32_t nch = 2 * d;
-  const LeafPlan p = leaf_plan(n, nch, n_leaves, LEAF_JMAX_DERIVED, LEAF_SPT_DERIVED);
+  const LeafPlan p = leaf_plan(n, nch, n_leaves, LEAF_JMAX_DERIVED);
   char* w = static_cast<char*>(ws);
   double* part = reinterpret_cast<double*>(w + leaf_ids_bytes(n));
   uint16_t* lab16 = reinterpret_cast<uint16_t*>(w + leaf_ids_bytes(n) + align256((int64_t)p.splits * n_leaves * nch * 8));
