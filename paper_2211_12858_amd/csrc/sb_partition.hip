@@ -680,6 +680,137 @@ __global__ void __launch_bounds__(PT_THREADS) k_part_scan_scatter(PartArgs a) {
   }
 }
 
+// ---------------------------------------------------------------- one-block partition
+// Small levels (up to PT_ONE_ROWS rows and PT_ONE_NODES nodes) in one launch
+// of one 1024-thread block: what k_part_flags_pick and k_part_scan_scatter do,
+// with the ballots, their prefix and the left-count bases in LDS.  Two
+// dependent launches cost such a level more than the work (10,000 rows: 10.7 us,
+// 9.0 us here, trees 110.7 -> 105.0 us; at 20,000 rows one block takes 15 us
+// against 12).  Thread
+// t takes the positions t + 1024 it, it < ITERS, so ballot 16 it + wave is the
+// ballot of 64 consecutive positions, in position order.
+constexpr int PT_ONE_THREADS = 1024;
+constexpr int64_t PT_ONE_ROWS = 10 * PT_ONE_THREADS;
+constexpr int PT_ONE_NODES = 32;
+
+template <bool PICK, int ITERS>
+__global__ void __launch_bounds__(PT_ONE_THREADS) k_part_one(PartArgs a) {
+  constexpr int WAVES = PT_ONE_THREADS / 64, NQ = ITERS * WAVES;
+  __shared__ uint64_t mk[NQ];
+  __shared__ int32_t pre[NQ], s_off[PT_ONE_NODES + 1], s_lb[PT_ONE_NODES + 1], sf[PT_ONE_NODES], sb[PT_ONE_NODES];
+  __shared__ int64_t sh[WAVES];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  int32_t row[ITERS];
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    const int64_t i = tid + (int64_t)it * PT_ONE_THREADS;
+    const int64_t ic = i < a.n ? i : a.n - 1;
+    const int64_t r = a.row_in ? (int64_t)a.row_in[ic] : ic;
+    row[it] = (int32_t)(r < 0 ? 0 : (r >= a.n ? a.n - 1 : r));
+  }
+  for (int j = tid; j <= a.n_nodes; j += PT_ONE_THREADS) s_off[j] = (int32_t)off_at(a, j);
+  if constexpr (PICK) {
+    for (int j = wave; j < a.n_nodes; j += WAVES) {
+      int32_t f, b;
+      double sc;
+      wave_best_feature(a.feat_s + (int64_t)j * a.m, a.feat_b + (int64_t)j * a.m, a.m, &f, &b, &sc);
+      if (lane == 0) {
+        sf[j] = f;
+        sb[j] = b;
+        a.out_f[j] = f;
+        a.out_b[j] = b;
+        a.out_s[j] = sc;
+      }
+    }
+  } else {
+    for (int j = tid; j < a.n_nodes; j += PT_ONE_THREADS) {
+      sf[j] = a.best_f[j];
+      sb[j] = a.best_b[j];
+    }
+  }
+  __syncthreads();
+  const NodeTab<true> tab{s_off, a.n};
+  const int64_t first = s_off[0], last = s_off[a.n_nodes];
+  // split of each position's node and its bin
+  {
+    int j = find_node<true>(tab, a.n_nodes, tid);
+    int64_t jend = s_off[j + 1];
+    int32_t bin[ITERS], most[ITERS];  // left: bin <= most
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+      const int64_t i = tid + (int64_t)it * PT_ONE_THREADS;
+      while (i >= jend && j < a.n_nodes - 1) {
+        ++j;
+        jend = s_off[j + 1];
+      }
+      // terminal node: every row goes left; positions outside the nodes are not flagged
+      const int32_t f = sf[j];
+      const bool live = i < a.n && i >= first && i < last, split = f >= 0 && f < a.m;
+      most[it] = live ? (split ? sb[j] : 255) : -1;
+      bin[it] = live && split ? (int32_t)a.bins_cm[(int64_t)f * a.ld_cm + row[it]] : 0;
+    }
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+      const uint64_t mask = __ballot(bin[it] <= most[it]);
+      if (lane == 0) mk[it * WAVES + wave] = mask;
+    }
+  }
+  __syncthreads();
+  const int64_t total = block_scan_nt<PT_ONE_THREADS>(
+      NQ, [&](int q) -> int64_t { return popc64(mk[q]); }, [&](int q, int64_t p) { pre[q] = (int32_t)p; }, sh);
+  __syncthreads();
+  // left flags before every node boundary, then the children
+  for (int j = tid; j <= a.n_nodes; j += PT_ONE_THREADS) {
+    const int x = s_off[j], q = x >> 6;
+    s_lb[j] = q < NQ ? pre[q] + popc64(mk[q] & ((uint64_t(1) << (x & 63)) - 1)) : (int32_t)total;
+  }
+  __syncthreads();
+  auto left_of = [&](int j, int64_t& size) { return node_left(s_off[j], s_off[j + 1], s_lb[j], s_lb[j + 1], &size); };
+  for (int j = tid; j < a.n_nodes; j += PT_ONE_THREADS) {
+    int64_t size;
+    const int64_t nl = left_of(j, size);
+    a.off_out[2 * j] = s_off[j];
+    a.off_out[2 * j + 1] = (int32_t)(s_off[j] + nl);
+    a.build_out[j] = (nl <= size - nl) ? 2 * j : 2 * j + 1;
+  }
+  if (tid == 0) a.off_out[2 * a.n_nodes] = s_off[a.n_nodes];
+  if (a.next_pre && wave == 0) {
+    // at most 64 nodes: one wave
+    int64_t size = 0, nl = 0;
+    if (lane < a.n_nodes) nl = left_of(lane, size);
+    const int32_t built = lane < a.n_nodes ? (int32_t)(nl <= size - nl ? nl : size - nl) : 0;
+    const int32_t incl = wave_incl_scan_i32(built);
+    if (lane < a.n_nodes) a.next_pre[lane] = incl - built;
+    if (lane == 63) a.next_pre[a.n_nodes] = incl;
+  }
+  // scatter
+  const uint64_t below = (uint64_t(1) << lane) - 1;
+  int j = find_node<true>(tab, a.n_nodes, tid);
+  int64_t jstart = s_off[j], jend = s_off[j + 1];
+  int64_t lbj = s_lb[j], nleft = (int64_t)s_lb[j + 1] - lbj;
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    const int64_t i = tid + (int64_t)it * PT_ONE_THREADS;
+    if (i < a.n && i >= first && i < last) {
+      while (i >= jend && j < a.n_nodes - 1) {
+        ++j;
+        jstart = jend;
+        jend = s_off[j + 1];
+        lbj = s_lb[j];
+        nleft = (int64_t)s_lb[j + 1] - lbj;
+      }
+      const int q = it * WAVES + wave;
+      const uint64_t m = mk[q];
+      const bool left = (m >> lane) & 1u;
+      const int64_t lrel = (int64_t)pre[q] + popc64(m & below) - lbj;
+      int64_t dest = left ? jstart + lrel : jstart + nleft + (i - jstart) - lrel;
+      dest = dest < 0 ? 0 : (dest >= a.n ? a.n - 1 : dest);
+      a.row_out[dest] = row[it];
+    }
+  }
+}
+static_assert(PT_ONE_NODES <= 64, "the built sizes are scanned by one wave");
+
 }  // namespace
 
 int32_t partition_scratch(void** out) {
@@ -750,6 +881,19 @@ int32_t launch_partition(const uint8_t* bins_cm, int64_t n, int32_t m, int64_t l
       a.out_f = const_cast<int32_t*>(best_f);
       a.out_b = const_cast<int32_t*>(best_b);
       a.out_s = best_s;
+    }
+    if (n <= PT_ONE_ROWS && n_nodes <= PT_ONE_NODES) {
+#define SB_ONE(I)                                                                                        \
+  do {                                                                                                   \
+    if (feat_s) hipLaunchKernelGGL((k_part_one<true, I>), dim3(1), dim3(PT_ONE_THREADS), 0, st, a);      \
+    else hipLaunchKernelGGL((k_part_one<false, I>), dim3(1), dim3(PT_ONE_THREADS), 0, st, a);            \
+  } while (0)
+      if (n <= 4 * PT_ONE_THREADS) SB_ONE(4);
+      else SB_ONE(10);
+#undef SB_ONE
+      return check_launch("sb_partition_rows");
+    }
+    if (feat_s) {
       hipLaunchKernelGGL(k_part_flags_pick<true>, dim3((unsigned)tiles), dim3(PT_THREADS), lf, st, a);
     } else {
       hipLaunchKernelGGL(k_part_flags_pick<false>, dim3((unsigned)tiles), dim3(PT_THREADS), lf, st, a);
