@@ -68,6 +68,7 @@ HistPlan hist_plan(int32_t m, int32_t n_bins, int32_t k, int32_t n_build, bool t
   p.pairs = (p.c + 1) / 2;
   if (p.c <= ROT_MAX_C && n_bins <= 256) {
     p.cg = (p.c + QROW_MAX_C - 1) / QROW_MAX_C;
+    p.gc = p.cg == 1 ? p.c : 2 * ((p.pairs + p.cg - 1) / p.cg);
     p.nq = ROT_F / 4;
     p.f = ROT_F;
     p.cells = 2 * p.pairs * p.f * n_bins;
@@ -427,14 +428,14 @@ k_quant_rows(const float* __restrict__ GH, int64_t ld_gh, int64_t n, const int32
   *reinterpret_cast<u32x4_a16*>(qrow + i * 4) = o;
 }
 
-// The same for 6 < c <= 6 CG channels: CG words per row, word g holding
-// channels 6g .. 6g + 5 (zero past c).  The row's c values come in 16-byte
+// The same for c > 6 channels: CG words per row, word g holding the GC (4 or 6)
+// channels GC g .. GC g + GC - 1 (zero past c).  The row's c values come in 16-byte
 // loads (dword-aligned), the last partial group of four as single loads.
-template <int CG>
+template <int CG, int GC>
 __global__ void __launch_bounds__(256)
 k_quant_rows_wide(const float* __restrict__ GH, int64_t ld_gh, int64_t n, int c, const int32_t* __restrict__ qexp,
                   uint32_t* __restrict__ qrow, int32_t* root_off, int64_t* root_pre) {
-  constexpr int CM = QROW_MAX_C * CG;
+  constexpr int CM = GC * CG;
   if (root_off && blockIdx.x == 0 && threadIdx.x == 0) {
     root_off[0] = 0;
     root_off[1] = (int32_t)n;
@@ -469,8 +470,8 @@ k_quant_rows_wide(const float* __restrict__ GH, int64_t ld_gh, int64_t n, int c,
   for (int g = 0; g < CG; ++g) {
     uint64_t half[2] = {0, 0};
 #pragma unroll
-    for (int jj = 0; jj < QROW_MAX_C; ++jj) {
-      const int t = QROW_MAX_C * g + jj;
+    for (int jj = 0; jj < GC; ++jj) {
+      const int t = GC * g + jj;
       const int32_t v = t < c ? (int32_t)rintf(ldexpf(__uint_as_float(w[t]), qe[t])) : 0;
       half[jj / 3] |= ((uint64_t)(uint32_t)v & M) << (QFIELD_BITS * (jj % 3));
     }
@@ -698,7 +699,7 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
     {
       const int pr = (tid >> 4) % P, bin0 = (tid >> 4) / P, fl = tid & (ROT_F - 1);
       int2* to = stage + pr * ps + fl * ld;
-      const int64_t at0 = (int64_t)((ROT_PMAX * grp + pr) * ROT_F + fl) * B;
+      const int64_t at0 = (int64_t)((P * grp + pr) * ROT_F + fl) * B;
 #pragma unroll
       for (int i = 0; i < ROT_CPT; ++i) {
         const int bin = bin0 + (ROT_ROWS / P) * i;
@@ -706,7 +707,7 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
         const bool fx = fits_partial(x), fy = fits_partial(y);
         if (bin < B && (FT == ROT_F || fl < FT)) {
           to[bin] = make_int2(fx ? (int32_t)x : PART_ESC, fy ? (int32_t)y : PART_ESC);
-          if (!(fx && fy) && ROT_PMAX * grp + pr < a.pairs) dov[at0 + bin] = make_longlong2(x, y);
+          if (!(fx && fy) && P * grp + pr < a.pairs) dov[at0 + bin] = make_longlong2(x, y);
         }
         tot[2 * i] = 0;
         tot[2 * i + 1] = 0;
@@ -714,14 +715,14 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
     }
     if (more) load_row_rot<FT, HAS_IDX>(a, r0, f0, qbase, qstride, d0);
     lds_barrier();
-    // this channel group's pairs are pairs 3 grp .. 3 grp + P - 1 of the
+    // this channel group's pairs are pairs P grp .. P grp + P - 1 of the
     // slot; pairs past the last (a short final group) and features past m
     // have no reader and are not written
     for (int rr = wave; rr < P * FT; rr += ROT_THREADS / 64) {
       const int pr = rr / FT, fl = rr - pr * FT;
-      if (ROT_PMAX * grp + pr >= a.pairs || f0 + fl >= a.m) continue;
+      if (P * grp + pr >= a.pairs || f0 + fl >= a.m) continue;
       const int2* from = stage + pr * ps + fl * ld;
-      int2* out = dst + (int64_t)((ROT_PMAX * grp + pr) * ROT_F + fl) * B;
+      int2* out = dst + (int64_t)((P * grp + pr) * ROT_F + fl) * B;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int bin = lane + 64 * u;
@@ -1184,12 +1185,14 @@ int32_t launch_build_histograms(const uint32_t* bins4, int64_t ld4, const uint8_
       case 5: hipLaunchKernelGGL(k_quant_rows<5>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, qexp, qrow, root_off, rp); break;
       case 6: hipLaunchKernelGGL(k_quant_rows<6>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, qexp, qrow, root_off, rp); break;
       default:
-        if (pl.cg == 2)
-          hipLaunchKernelGGL(k_quant_rows_wide<2>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, pl.c, qexp, qrow, root_off, rp);
+        if (pl.cg == 2 && pl.gc == 4)
+          hipLaunchKernelGGL((k_quant_rows_wide<2, 4>), dim3(qb), dim3(256), 0, st, GH, ld_gh, n, pl.c, qexp, qrow, root_off, rp);
+        else if (pl.cg == 2)
+          hipLaunchKernelGGL((k_quant_rows_wide<2, 6>), dim3(qb), dim3(256), 0, st, GH, ld_gh, n, pl.c, qexp, qrow, root_off, rp);
         else if (pl.cg == 3)
-          hipLaunchKernelGGL(k_quant_rows_wide<3>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, pl.c, qexp, qrow, root_off, rp);
+          hipLaunchKernelGGL((k_quant_rows_wide<3, 6>), dim3(qb), dim3(256), 0, st, GH, ld_gh, n, pl.c, qexp, qrow, root_off, rp);
         else
-          hipLaunchKernelGGL(k_quant_rows_wide<4>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, pl.c, qexp, qrow, root_off, rp);
+          hipLaunchKernelGGL((k_quant_rows_wide<4, 6>), dim3(qb), dim3(256), 0, st, GH, ld_gh, n, pl.c, qexp, qrow, root_off, rp);
         break;
     }
   }
@@ -1221,8 +1224,8 @@ int32_t launch_build_histograms(const uint32_t* bins4, int64_t ld4, const uint8_
   if (prof) (void)hipEventRecord(e0, st);
   const size_t lds_bytes = ROT_LDS_BYTES;
   // up to six channels: one workgroup per (slice, row group); more: channel
-  // groups of six (three pairs) each, one workgroup per (slice, group)
-  switch (pl.c) {
+  // groups of four or six, one workgroup per (slice, group)
+  switch (pl.gc) {
     case 1: hipLaunchKernelGGL(k_hist_rot<1>, dim3(grid), dim3(ROT_THREADS), lds_bytes, st, a); break;
     case 2: hipLaunchKernelGGL(k_hist_rot<2>, dim3(grid), dim3(ROT_THREADS), lds_bytes, st, a); break;
     case 3: hipLaunchKernelGGL(k_hist_rot<3>, dim3(grid), dim3(ROT_THREADS), lds_bytes, st, a); break;

@@ -47,7 +47,7 @@ def case(n, m, B, k, seed):
 # of 32; one to three channel groups
 @pytest.mark.parametrize("n,m,B,k", [(1, 1, 2, 1), (767, 16, 256, 5), (768, 17, 255, 5), (769, 18, 33, 4),
                                      (1537, 20, 34, 3), (5000, 24, 2, 2), (9000, 31, 64, 10), (3000, 49, 256, 16),
-                                     (70_001, 300, 16, 5)])
+                                     (70_001, 300, 16, 5), (9000, 20, 256, 6), (9001, 33, 255, 7)])
 def test_root_histograms_exact(n, m, B, k):
     bins, GH, qexp = case(n, m, B, k, seed=n + m)
     off = np.array([0, n], dtype=np.int32)
@@ -57,7 +57,7 @@ def test_root_histograms_exact(n, m, B, k):
 
 @pytest.mark.parametrize("sizes,m,B,k", [([1, 0, 1, 1], 3, 256, 5), ([0, 0, 767, 0, 1, 768, 0], 17, 255, 5),
                                          ([2000, 1, 0, 3000, 769], 20, 33, 10), ([40_000, 5, 25_000], 260, 8, 5),
-                                         ([7] * 40, 33, 64, 23)])
+                                         ([7] * 40, 33, 64, 23), ([3000, 0, 1500], 18, 256, 7), ([900, 5], 40, 64, 6)])
 def test_gathered_histograms_exact(sizes, m, B, k):
     n = sum(sizes) + 11
     bins, GH, qexp = case(n, m, B, k, seed=len(sizes) + m)
