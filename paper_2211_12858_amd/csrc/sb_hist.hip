@@ -591,7 +591,7 @@ __device__ inline void run_segment_rot(const HistArgs& a, lds_u64* lds, int64_t*
       // the second barrier keeps the next window's adds behind every fold
       // read, so a cell's change between two reads is one window's rows
       lds_barrier();
-      fold_cells<ROT_CPT, ROT_THREADS>((const uint64_t*)lds, tot);
+      fold_cells<rot_cpt((C + 1) / 2), ROT_THREADS>((const uint64_t*)lds, tot);
       lds_barrier();
     }
   }
@@ -616,7 +616,7 @@ __device__ inline int64_t sum_copies(int64_t x) {
 }
 
 // One workgroup's share of a level: the slice's cells in [bin][pair][slot]
-// order, thread t owning the 64-bit cells t + ROT_THREADS * i, i < ROT_CPT.
+// order, thread t owning the 64-bit cells t + ROT_THREADS * i, i < rot_cpt(P).
 // At the end of a node's part the totals go out through LDS, all pairs at
 // once, as int32 partials laid out [pair][feature][bin].  (One pair at a time
 // through 16-byte int64 pairs, two barriers each, a node's end cost 11 us: 29
@@ -627,7 +627,7 @@ __device__ inline int64_t sum_copies(int64_t x) {
 template <int C, int FT, bool HAS_IDX>
 __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds64, int64_t T, int s, int grp, int q,
                                                int qn) {
-  constexpr int P = (C + 1) / 2;
+  constexpr int P = (C + 1) / 2, CPT = rot_cpt(P);
   const int64_t v0 = (int64_t)q * T / qn;
   const int64_t v1 = (int64_t)(q + 1) * T / qn;
   if (v0 >= v1) return;
@@ -656,11 +656,11 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
 
   Segment sg = segment(p, v0);
   RowRef r0 = row_at<HAS_IDX>(a, sg, sg.v, tid), r1 = row_at<HAS_IDX>(a, sg, sg.v + ROT_THREADS, tid);
-  int64_t tot[2 * ROT_CPT];
+  int64_t tot[2 * CPT];
 #pragma unroll
-  for (int jj = 0; jj < 2 * ROT_CPT; ++jj) tot[jj] = 0;
+  for (int jj = 0; jj < 2 * CPT; ++jj) tot[jj] = 0;
 #pragma unroll
-  for (int i = 0; i < ROT_CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
+  for (int i = 0; i < CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
   RowRot<FT> d0;
   load_row_rot<FT, HAS_IDX>(a, r0, f0, qbase, qstride, d0);
   lds_barrier();
@@ -689,7 +689,7 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
     // The node-end barriers wait for LDS operations only: the partial stores
     // take their data from registers, so nothing here waits for them.
     lds_barrier();
-    fold_cells<ROT_CPT, ROT_THREADS>(lds64, tot);
+    fold_cells<CPT, ROT_THREADS>(lds64, tot);
     lds_barrier();  // every fold read is done: the LDS becomes the staging area
     const int64_t slot = ((int64_t)s * a.slots + q + pend) * a.cells;  // channel cells
     int2* dst = reinterpret_cast<int2*>(a.part32 + slot);
@@ -701,7 +701,7 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
       int2* to = stage + pr * ps + fl * ld;
       const int64_t at0 = (int64_t)((P * grp + pr) * ROT_F + fl) * B;
 #pragma unroll
-      for (int i = 0; i < ROT_CPT; ++i) {
+      for (int i = 0; i < CPT; ++i) {
         const int bin = bin0 + (ROT_ROWS / P) * i;
         const int64_t x = sum_copies<FT>(tot[2 * i]), y = sum_copies<FT>(tot[2 * i + 1]);
         const bool fx = fits_partial(x), fy = fits_partial(y);
@@ -732,7 +732,7 @@ __device__ __forceinline__ void hist_rot_group(const HistArgs& a, uint64_t* lds6
     if (!more) return;
     lds_barrier();
 #pragma unroll
-    for (int i = 0; i < ROT_CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
+    for (int i = 0; i < CPT; ++i) lds64[tid + ROT_THREADS * i] = 0;
     lds_barrier();
   }
 }
@@ -1178,7 +1178,6 @@ int32_t launch_build_histograms(const uint32_t* bins4, int64_t ld4, const uint8_
     const unsigned qb = (unsigned)((n + 255) / 256);
     int64_t* rp = const_cast<int64_t*>(pre_given);
     switch (pl.c) {
-      case 1: hipLaunchKernelGGL(k_quant_rows<1>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, qexp, qrow, root_off, rp); break;
       case 2: hipLaunchKernelGGL(k_quant_rows<2>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, qexp, qrow, root_off, rp); break;
       case 3: hipLaunchKernelGGL(k_quant_rows<3>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, qexp, qrow, root_off, rp); break;
       case 4: hipLaunchKernelGGL(k_quant_rows<4>, dim3(qb), dim3(256), 0, st, GH, ld_gh, n, qexp, qrow, root_off, rp); break;
@@ -1226,7 +1225,6 @@ int32_t launch_build_histograms(const uint32_t* bins4, int64_t ld4, const uint8_
   // up to six channels: one workgroup per (slice, row group); more: channel
   // groups of four or six, one workgroup per (slice, group)
   switch (pl.gc) {
-    case 1: hipLaunchKernelGGL(k_hist_rot<1>, dim3(grid), dim3(ROT_THREADS), lds_bytes, st, a); break;
     case 2: hipLaunchKernelGGL(k_hist_rot<2>, dim3(grid), dim3(ROT_THREADS), lds_bytes, st, a); break;
     case 3: hipLaunchKernelGGL(k_hist_rot<3>, dim3(grid), dim3(ROT_THREADS), lds_bytes, st, a); break;
     case 4: hipLaunchKernelGGL(k_hist_rot<4>, dim3(grid), dim3(ROT_THREADS), lds_bytes, st, a); break;

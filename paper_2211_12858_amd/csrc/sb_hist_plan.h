@@ -42,12 +42,16 @@ constexpr int GROUP_MIN_ROWS = 768;
 // One histogram workgroup: 768 threads (12 waves, 3 per SIMD) and the cells
 // of a slice of 16 features for up to 3 channel pairs (c <= 6), laid out
 // [bin][pair][feature] for 256 bins (12288 64-bit cells, 96 KB of the
-// 160 KB LDS), ROT_CPT cells per thread.
+// 160 KB LDS), rot_cpt(pairs) cells per thread.
 constexpr int ROT_THREADS = 768;
 constexpr int ROT_F = 16;
 constexpr int ROT_PMAX = 3;
 constexpr int ROT_CELLS = 256 * ROT_PMAX * ROT_F;
-constexpr int ROT_CPT = ROT_CELLS / ROT_THREADS;
+// Cells per thread of a workgroup with that many pairs: 6, 11 and 16.  (With 16
+// for every count, 47 registers spilled with one pair and 12 with two once a node's
+// end also held the next node's rows: trees of 2M x 100 at k = 1 637 us, 609 so; two
+// gathered nodes of 1M x 20 at 32 bins, k = 1, 40.8 and 38.4 us.)
+constexpr int rot_cpt(int pairs) { return (256 * pairs * ROT_F + ROT_THREADS - 1) / ROT_THREADS; }
 constexpr int ROT_ROWS = ROT_THREADS / ROT_F;  // rows of 16 cells that the workgroup touches at once
 static_assert(ROT_ROWS % 2 == 0 && ROT_ROWS % 3 == 0, "a thread's cells must share one pair");
 // Staging of a node's partials in the same LDS: rows of rot_stage_ld(n_bins)
@@ -55,7 +59,7 @@ static_assert(ROT_ROWS % 2 == 0 && ROT_ROWS % 3 == 0, "a thread's cells must sha
 constexpr int rot_stage_ld(int n_bins) { return (n_bins + 29) / 32 * 32 + 2; }
 constexpr int ROT_STAGE_PAIRS = ROT_PMAX * (ROT_F * rot_stage_ld(256) + 1);
 constexpr int ROT_LDS_BYTES = 8 * (ROT_STAGE_PAIRS > ROT_CELLS ? ROT_STAGE_PAIRS : ROT_CELLS);
-static_assert(ROT_CPT * ROT_THREADS == ROT_CELLS, "rotated cells must split evenly over the threads");
+static_assert(rot_cpt(ROT_PMAX) * ROT_THREADS == ROT_CELLS, "the threads' cells must lie in the LDS");
 static_assert(WINDOW_ROWS % ROT_THREADS == 0, "a fixed-point window must be a whole number of steps");
 
 struct HistPlan {
