@@ -625,39 +625,50 @@ k_project_sparse(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, co
 // same flops per clock as the 32 x 32 x 2 form, and MI355X's fp32 MFMA rate is
 // twice its fp32 vector rate without packed instructions, so at k >= 8 the
 // product stops being bound by the VALU.
-// A wave computes 64 M4_MT rows x 4 * NG sketch columns; lane l loads the M4_MT
-// consecutive rows M4_MT l + e of a column in one load, and component
-// e of all lanes is one A operand.  Operands:
-//   A (block b, 4 x 1): lane l holds G[row0 + M4_MT l + e, j];
+// A wave computes 64 M4_MT rows x 4 * NG sketch columns.  Lane l has M4_MT of
+// them, row(l, e) for e < M4_MT: consecutive ones, row0 + M4_MT l + e, in one load
+// (PAIRS), or one of each run of 64, row0 + 64 e + l; its values of component e are
+// one A operand.  Operands:
+//   A (block b, 4 x 1): lane l holds G[row(l, e), j];
 //   B (block b, 1 x 4): lane l holds Pi[j, t0 + 4g + l % 4], the same in
 //     every block, read from a block of Pi staged in LDS (zero past d and
 //     past the pass's kt columns: four addresses per read, a broadcast);
-//   D (block b, 4 x 4): register r of lane l holds row
-//     row0 + M4_MT (4 (l / 4) + r) + e, column t0 + 4g + l % 4.
+//   D (block b, 4 x 4): register r of lane l holds row row(4 (l / 4) + r, e),
+//     column t0 + 4g + l % 4.
 // KU columns of G are loaded before their MFMAs.  The order in which the
 // hardware adds the products is its own, so the result is checked against
 // the exact product with the dot-product error bound.
-// Blocks of 16 waves read 8 KB runs of a column where 4 waves read 2 KB: the
-// read of G bounds the kernel, and longer runs read faster (2M x 1000 -> 20:
-// 1467 against 1590 us; 8 waves 1540; four rows per lane 1810, for want of
-// waves).  4 waves stay where 16-wave blocks (one per CU) would leave the last
-// round of blocks part-empty.
+//
+// Blocks of 16 waves (always PAIRS) read 8 KB runs of a column where 4 waves
+// read 2 KB: the read of G bounds the kernel, and longer runs read faster (2M x
+// 1000 -> 20: 1454 against 1579 us; 8 waves 1540; four rows per lane 1810, for
+// want of waves).  But such a block is alone on its CU: nothing runs there while
+// it stages Pi and writes its rows, which a block of few columns of G does for
+// most of its time.  So 4 waves stay where the last round of 16-wave blocks would
+// be part-empty, and below the column counts of big_projection().
+//
+// In blocks of 4 waves the compiler decides how many loads of a batch are in
+// flight: with pairs it waits for the first ones after three or four loads at 2,
+// 3, 6 and 7 groups (50,000 x 1000 -> 8: 155 us, 106 us in runs; -> 24: 189 and
+// 163), and issues the whole batch at 4, 5 and 8 (200,000 x 1000 -> 20: 176 us,
+// 181 us in runs).
 constexpr int M4_SMALL = 256, M4_BIG = 1024;  // threads per block
 constexpr int M4_BIG_MAX_NG = 6;              // groups of 4 columns that 16 waves' 128 registers hold
-constexpr int M4_MT = 2;    // consecutive rows per lane
+constexpr int M4_MT = 2;    // rows per lane
 constexpr int M4_JC = 256;  // columns of G per staged block of Pi
 // columns of G per batch of loads (16 waves have 128 registers each)
 constexpr int m4_ku(int ng, int threads) { return threads == M4_BIG && ng > 5 ? 8 : 16; }
+constexpr bool m4_pairs(int ng, int threads) { return threads == M4_BIG || ng == 4 || ng == 5 || ng == 8; }
 static_assert(M4_JC % 16 == 0, "a batch of columns never passes the staged block");
 typedef float mf_v4 __attribute__((ext_vector_type(4)));
 // M4_MT consecutive values from a 4-byte aligned address, streamed
 typedef float mf_rows __attribute__((ext_vector_type(M4_MT), aligned(4)));
 
-// The products of one tile's columns [j0, j0 + jc) (Pi staged in sPi).  FULL:
-// every lane's rows exist; else a row past the end reads row n - 1 (its
-// results are not stored).
-template <int NG, int KU, bool FULL>
-__device__ __forceinline__ void project_columns(const float* __restrict__ G, int64_t ld_g, int64_t row, int64_t n,
+// The products of one tile's columns [j0, j0 + jc) (Pi staged in sPi) with the
+// lane's rows rc, those past the end clamped to row n - 1 (their results are not
+// stored).  PAIRS: the rows are consecutive where FULL.
+template <int NG, int KU, bool PAIRS, bool FULL>
+__device__ __forceinline__ void project_columns(const float* __restrict__ G, int64_t ld_g, const int64_t (&rc)[M4_MT],
                                                 int j0, int jc, const float* sPi, mf_v4 (&acc)[M4_MT][NG]) {
   constexpr int W = 4 * NG;
   const int cq = threadIdx.x & 3;  // this lane's column within each group of 4
@@ -667,11 +678,11 @@ __device__ __forceinline__ void project_columns(const float* __restrict__ G, int
     for (int u = 0; u < KU; ++u) {
       // past the block: a finite value of column jc - 1 times a zero of Pi
       const float* col = G + (int64_t)(j0 + (kk + u < jc ? kk + u : jc - 1)) * ld_g;
-      if constexpr (FULL) {
-        a[u] = __builtin_nontemporal_load(reinterpret_cast<const mf_rows*>(col + row));
+      if constexpr (PAIRS && FULL) {
+        a[u] = __builtin_nontemporal_load(reinterpret_cast<const mf_rows*>(col + rc[0]));
       } else {
 #pragma unroll
-        for (int e = 0; e < M4_MT; ++e) a[u][e] = col[row + e < n ? row + e : n - 1];
+        for (int e = 0; e < M4_MT; ++e) a[u][e] = ld_stream(col + rc[e]);
       }
     }
 #pragma unroll
@@ -695,6 +706,7 @@ k_project_mfma4(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, con
                 uint32_t* __restrict__ blockmax) {
   constexpr int W = 4 * NG;  // sketch columns of the pass, padded to a multiple of 4
   constexpr int KU = m4_ku(NG, THREADS);
+  constexpr bool PAIRS = m4_pairs(NG, THREADS);
   __shared__ float sPi[M4_JC * W];
   __shared__ uint32_t smax[THREADS / 64][W + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -708,6 +720,10 @@ k_project_mfma4(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, con
   for (int64_t base = (int64_t)blockIdx.x * ROWS; base < n; base += (int64_t)gridDim.x * ROWS) {
     const int64_t rw = base + (int64_t)wave * M4_MT * 64;
     const bool full = rw + M4_MT * 64 <= n;
+    auto row_of = [&](int l, int e) { return rw + (PAIRS ? M4_MT * l + e : 64 * e + l); };
+    int64_t rc[M4_MT];
+#pragma unroll
+    for (int e = 0; e < M4_MT; ++e) rc[e] = row_of(lane, e) < n ? row_of(lane, e) : n - 1;
     mf_v4 acc[M4_MT][NG];
 #pragma unroll
     for (int e = 0; e < M4_MT; ++e)
@@ -721,8 +737,8 @@ k_project_mfma4(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, con
         sPi[e] = (jr < jc && c < kt) ? Pi[(int64_t)(j0 + jr) * k + t0 + c] : 0.0f;
       }
       __syncthreads();
-      if (full) project_columns<NG, KU, true>(G, ld_g, rw + M4_MT * lane, n, j0, jc, sPi, acc);
-      else project_columns<NG, KU, false>(G, ld_g, rw + M4_MT * lane, n, j0, jc, sPi, acc);
+      if (PAIRS && full) project_columns<NG, KU, PAIRS, true>(G, ld_g, rc, j0, jc, sPi, acc);
+      else project_columns<NG, KU, PAIRS, false>(G, ld_g, rc, j0, jc, sPi, acc);
     }
 #pragma unroll
     for (int e = 0; e < M4_MT; ++e)
@@ -731,7 +747,7 @@ k_project_mfma4(const float* __restrict__ G, int64_t n, int d, int64_t ld_g, con
         const int col = 4 * g + cq;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int64_t row = rw + M4_MT * (4 * (lane >> 2) + r) + e;
+          const int64_t row = row_of(4 * (lane >> 2) + r, e);
           if (row < n && col < kt) {
             const float v = acc[e][g][r];
             GH[row * ld_gh + t0 + col] = v;
@@ -882,29 +898,51 @@ SketchWs sketch_ws_layout(int64_t n, int32_t d, int32_t k) {
   return L;
 }
 
+// Whether the projection takes 16-wave blocks: where they fill at least 0.9 of
+// their rounds over the CUs, a pass's columns fit their registers, and G has
+// enough columns that a block's start and end weigh little.  16 against 4 waves, in
+// us, at k = 8 / 20:
+//   one round      480,000 x 50    47.0 / 56.3 and  44.8 / 58.6
+//                  480,000 x 100   58.9 / 67.8 and  58.9 / 72.2
+//   two rounds     1M x 100       126.5 / 139.2 and 117.2 / 136.4
+//                  1M x 200       183.9 / 200.9 and 178.7 / 204.0
+//                  943,000 x 200  0.88 / 0.94 of the time of 4 waves
+//   four rounds    2M x 200       371.5 / 398.5 and 347.8 / 398.9
+//                  2M x 300       489.7 / 553.5 and 481.9 / 542.9
+//                  2M x 500       736.4 / 796.7 and 750.5 / 844.7
+// (At 2,090,000 rows 13 to 20 columns take 1 to 12% longer in 16 waves, at 2,080,000 and
+// 2,050,000 3 to 10% less: an effect of the leading dimension that no size rule catches.)
+// 24 columns, whose rows in steps of 8 floats are whole 128-byte lines, are faster in
+// 16 waves at any width (2M x 30 205 against 259).
+bool big_projection(int64_t n, int32_t d, int32_t k) {
+  const int64_t blocks = (n + M4_BIG * M4_MT - 1) / (M4_BIG * M4_MT), rounds = (blocks + 255) / 256;
+  if (blocks < rounds * 256 * 9 / 10 || k > 4 * M4_BIG_MAX_NG) return false;
+  return k > 23 || d >= (rounds > 2 ? 300 : rounds == 2 ? 200 : k > 12 ? 50 : 100);
+}
+
 // G Pi for a dense Pi, PROJ_KT sketch columns per pass; returns the grid size
 // (block b's maxima of every channel sit in row b of blockmax).
 int launch_dense_projection(const float* G, int64_t n, int32_t d, int64_t ld_g, const float* h, int32_t k,
                             const float* Pi, float* GH, int64_t ld_gh, uint32_t* blockmax, hipStream_t st) {
   if (k >= PROJ_MFMA_MIN_K) {
-    // 16-wave blocks where they fill at least 0.9 of their rounds over the CUs
-    // and a pass's columns fit their registers
-    const int64_t big = (n + M4_BIG * M4_MT - 1) / (M4_BIG * M4_MT), rounds = (big + 255) / 256;
-    const int threads = big >= rounds * 256 * 9 / 10 && k <= 4 * M4_BIG_MAX_NG ? M4_BIG : M4_SMALL;
+    const int threads = big_projection(n, d, k) ? M4_BIG : M4_SMALL;
     const int nb = sketch_blocks(n, threads * M4_MT, SKETCH_MAX_BLOCKS);
     for (int t0 = 0; t0 < k; t0 += 32) {
       const int ng = (k - t0 < 32 ? k - t0 + 3 : 32 + 3) / 4;
+// (16-wave blocks take 8 to 24 columns, 2 to 6 groups: the other cases name an instance that is there)
+#define M4_BIG_NG(NG) ((NG) >= 2 && (NG) <= M4_BIG_MAX_NG ? (NG) : 2)
 #define SB_P4(NG)                                                                                              \
   case NG:                                                                                                     \
     if (threads == M4_BIG)                                                                                     \
-      hipLaunchKernelGGL((k_project_mfma4<(NG <= M4_BIG_MAX_NG ? NG : 1), M4_BIG>), dim3(nb), dim3(M4_BIG), 0, st, G, n, d, ld_g, Pi, k,   \
-                         t0, h, GH, ld_gh, blockmax);                                                          \
+      hipLaunchKernelGGL((k_project_mfma4<M4_BIG_NG(NG), M4_BIG>), dim3(nb), dim3(M4_BIG), 0, st, G, n, d,     \
+                         ld_g, Pi, k, t0, h, GH, ld_gh, blockmax);                                             \
     else                                                                                                       \
       hipLaunchKernelGGL((k_project_mfma4<NG, M4_SMALL>), dim3(nb), dim3(M4_SMALL), 0, st, G, n, d, ld_g, Pi,  \
                          k, t0, h, GH, ld_gh, blockmax);                                                       \
     break;
       switch (ng) { SB_P4(1) SB_P4(2) SB_P4(3) SB_P4(4) SB_P4(5) SB_P4(6) SB_P4(7) SB_P4(8) }
 #undef SB_P4
+#undef M4_BIG_NG
     }
     return nb;
   }

@@ -35,7 +35,8 @@ def spilled_registers(source, tmp_path):
     return {re.sub(r"\(anonymous namespace\)::|sb::|void ", "", n).split("(")[0]: v for n, v in zip(names, out.values())}
 
 
-@pytest.mark.parametrize("source,kernel,instances", [("sb_hist.hip", "k_hist_rot<", 5)])
+@pytest.mark.parametrize("source,kernel,instances", [("sb_hist.hip", "k_hist_rot<", 5),
+                                                      ("sb_sketch.hip", "k_project_mfma4<", 13)])
 def test_no_spilled_registers(source, kernel, instances, tmp_path):
     spilled = {n: v for n, v in spilled_registers(source, tmp_path).items() if n.startswith(kernel)}
     assert len(spilled) == instances
