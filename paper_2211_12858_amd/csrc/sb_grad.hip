@@ -19,7 +19,8 @@
 //   same thread of the same block, in tile order).  k_grad_norm_final adds the
 //   slots in a fixed order, so the norms are deterministic and the same for
 //   every grid that divides the slot count (the fused update below launches
-//   fewer blocks than the derivatives alone).
+//   fewer blocks than the derivatives alone).  k_grad_softmax_wide has a partial
+//   per block instead, and a grid that follows from the shape (sb_grad_plan.h).
 // k_update: F[i, j] += lr * V[leaf of i, j] in fp64, rounded once to fp32.
 //   lr * V of a chunk of columns is staged in LDS; the leaf ids come from the
 //   leaf segments (k_leaf_ids, shared with the leaf values).
@@ -32,6 +33,7 @@
 #include <cmath>
 
 #include "sb_common.h"
+#include "sb_grad_plan.h"
 #include "sb_leaf_ids.h"
 
 namespace sb {
@@ -477,9 +479,6 @@ __device__ inline void swap_rows(float& x, float& y) {  // x's odd rows of 16 la
   y = __uint_as_float(r[1]);
 }
 
-constexpr int WIDE_C = 32;  // columns per lane
-constexpr int WIDE_MAX_WAVES = 16;
-constexpr int WIDE_MAX_D = 64 * WIDE_MAX_WAVES;
 // lane offsets within a wave's columns are 32-bit byte offsets
 constexpr int64_t WIDE_MAX_LD = int64_t(1) << 24;
 
@@ -630,8 +629,11 @@ __device__ __forceinline__ void softmax_wide_wave(const GradArgs& a, float (*sre
   if (a.npart && lane < 32 * PARTS && col < a.d) a.npart[(int64_t)col * a.n_parts + bx] = total;
 }
 
+// Five waves per SIMD: with hessians and 32 rows the compiler otherwise takes 97
+// registers, one too many, and a CU holds one block of 9 or 10 waves instead of two.
 template <int ROWS, bool HESS>
-__global__ void __launch_bounds__(64 * WIDE_MAX_WAVES) k_grad_softmax_wide(GradArgs a, int grid, int tiles) {
+__global__ void __launch_bounds__(64 * WIDE_MAX_WAVES)
+k_grad_softmax_wide(GradArgs a, int grid, int tiles) {
   __shared__ float sred[3][WIDE_MAX_WAVES][64];
   // each XCD takes a run of neighbouring tiles (see k_update_sigmoid)
   const int bx = (int)(blockIdx.x & 7) * ((grid + 7) >> 3) + (int)(blockIdx.x >> 3);
@@ -759,28 +761,15 @@ void launch_softmax_regs(const GradArgs& a, size_t lds, hipStream_t st) {
   }
 }
 
-// The register softmax kernel for 104 < d <= 1024: 64 rows x 32 columns per
-// wave (up to 16 waves) or, past 512 columns, 32 rows x 64.  As many blocks as
-// fit at once, each with the same number of tiles, and no more than the norm
-// partials' slots (GradArgs::n_parts on entry); returns the blocks, the
-// partials' stride.
+// The register softmax kernel for 104 < d <= 1024, split by wide_plan(); returns
+// the blocks, the partials' stride.
 int launch_softmax_wide(GradArgs a, hipStream_t st) {
-  const int which = a.d <= WIDE_C * WIDE_MAX_WAVES ? 0 : 1, rows = which == 0 ? 64 : 32;
-  const int wc = WIDE_C * (64 / rows), threads = 64 * ((a.d + wc - 1) / wc);
-  const int tiles = (int)((a.n + rows - 1) / rows);
-  static thread_local int fit_threads[2] = {0, 0}, fit[2] = {0, 0};  // per-thread cache of the occupancy query
-  if (fit_threads[which] != threads) {
-    fit[which] = which == 0 ? resident_blocks(k_grad_softmax_wide<64, false>, threads)
-                            : resident_blocks(k_grad_softmax_wide<32, false>, threads);
-    fit_threads[which] = threads;
-  }
-  int most = fit[which] < a.n_parts ? fit[which] : a.n_parts;
-  if (most > tiles) most = tiles;
-  const int per = (tiles + most - 1) / most, grid = (tiles + per - 1) / per;
+  const WidePlan p = wide_plan(a.n, a.d, a.n_parts);
+  const int threads = 64 * p.waves, grid = p.grid, tiles = p.tiles;
   a.n_parts = grid;
   const dim3 blocks((grid + 7) / 8 * 8);
 #define SB_WIDE(R, H) hipLaunchKernelGGL((k_grad_softmax_wide<R, H>), blocks, dim3(threads), 0, st, a, grid, tiles)
-  if (which == 0) { if (a.hess) SB_WIDE(64, true); else SB_WIDE(64, false); }
+  if (p.rows == 64) { if (a.hess) SB_WIDE(64, true); else SB_WIDE(64, false); }
   else if (a.hess) SB_WIDE(32, true);
   else SB_WIDE(32, false);
 #undef SB_WIDE
