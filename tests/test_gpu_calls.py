@@ -346,8 +346,8 @@ def test_histograms_int32_partials_escape(gathered):
     bin, with channels of +-(1 - 2^-24), whose
     fixed-point images are +-2^18.  Those cells take the exact int64 overflow
     slot; every cell must still match the oracle within the fixed-point bound.
-    With 100 features a slice has 32 (gathered) to 40 (root) row groups, so a
-    workgroup holds 12,500 to 15,000 rows."""
+    With 100 features a slice has 36 (gathered) or 40 (root) row groups, so a
+    workgroup holds 11,093 or 15,000 rows."""
     rng = np.random.default_rng(321)
     n, m, B, k = 600_000, 100, 8, 5
     bins = rng.integers(0, B, size=(n, m), dtype=np.uint8)

@@ -209,7 +209,10 @@ def test_fused_level_end_escaped_partials():
     """Whole trees whose partial sums leave int32 (a constant feature and
     full-scale same-sign gradient columns, 600,000 rows): the fused level end
     of sb_grow_tree and the per-step calls (whose histograms are checked
-    against the oracle on such data) grow the same tree bit for bit."""
+    against the oracle on such data) grow the same tree bit for bit.  The cells
+    that escape here are the constant feature's, which is never split on;
+    test_tree_with_escaped_sums (test_gpu_hist_edges.py) has split features whose
+    sums escape."""
     rng = np.random.default_rng(77)
     n, m, B, k, depth = 600_000, 100, 16, 5, 5
     bins = rng.integers(0, B, size=(n, m), dtype=np.uint8)
