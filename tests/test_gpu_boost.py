@@ -38,9 +38,13 @@ U = 2.0 ** -24
 SUB = 4 * 2.0 ** -149  # values below fp32's normal range carry absolute, not relative, rounding
 
 
-def run_gradients(loss, F_T, target, want_hess=True, want_row=True, want_norms=True):
+def run_gradients(loss, F_T, target, want_hess=True, want_row=True, want_norms=True, ld_f=None):
     d, n = F_T.shape
     Fd = gu.up(F_T)
+    if ld_f is not None:
+        wide = torch.empty((d, ld_f), dtype=torch.float32, device=gu.DEV)
+        wide[:, :n] = Fd
+        Fd = wide
     G = torch.full((d, n), float("nan"), dtype=torch.float32, device=gu.DEV)
     H = torch.full((d, n), float("nan"), dtype=torch.float32, device=gu.DEV) if want_hess else None
     hr = torch.full((n,), float("nan"), dtype=torch.float32, device=gu.DEV) if want_row else None
@@ -48,7 +52,7 @@ def run_gradients(loss, F_T, target, want_hess=True, want_row=True, want_norms=T
     ws = workspace(L.sb_workspace_bytes(L.SB_CALL_GRADIENTS, n=n, d=d), gu.DEV)
     labels = gu.up(target) if loss == "softmax" else None
     Y = gu.up(target) if loss == "sigmoid" else None
-    L.sb_gradients(L.LOSS[loss], Fd, n, d, n, labels, Y, n, G, n, H, n, hr, n2, ws, ws.numel())
+    L.sb_gradients(L.LOSS[loss], Fd, n, d, n if ld_f is None else ld_f, labels, Y, n, G, n, H, n, hr, n2, ws, ws.numel())
     gu.sync()
     out = [G.cpu().numpy()]
     out.append(H.cpu().numpy() if want_hess else None)
@@ -78,10 +82,10 @@ def grad_tolerances(loss, F_T, target):
     return g, h, tg, th
 
 
-def check_gradients(loss, F_T, target):
+def check_gradients(loss, F_T, target, ld_f=None):
     d, n = F_T.shape
     print("gradients case: %s d=%d n=%d" % (loss, d, n), flush=True)
-    G, H, hr, n2 = run_gradients(loss, F_T, target)
+    G, H, hr, n2 = run_gradients(loss, F_T, target, ld_f=ld_f)
     tgt = target if loss == "softmax" else target.T
     G_o, H_o, hr_o, n2_o = ob.gradients(loss, F_T.T, tgt)
     _, _, tg, th = grad_tolerances(loss, F_T, target)
@@ -97,8 +101,9 @@ def check_gradients(loss, F_T, target):
     return G, H, hr, n2
 
 
-# d at and around each kernel boundary: rows held in registers for d <= 16,
-# 32, 64, 104, the two-pass kernel above (ragged last column chunks)
+# d at and around each kernel boundary: rows held in the registers of a thread for
+# d <= 16, 32, 64, 104, in those of a block above (test_gpu_grad_edges.py has that
+# kernel's own edges, and the two-pass kernel past 1024)
 @pytest.mark.parametrize("d", [1, 5, 16, 17, 32, 64, 100, 104, 105, 130, 257])
 def test_softmax_gradients(d):
     F_T, y = scores_and_targets(3 * 256 + 77, d, "softmax", seed=d, scale=2.0)
@@ -157,9 +162,10 @@ def test_update_predictions_bit_exact(n_leaves, d):
 
 
 # The fused update + derivatives against the two calls it stands for, bit for
-# bit: the one-pass kernel (softmax, d <= 104, <= 256 leaves whose lr * V
-# table fits 64 KB) at each register-kernel width and ragged tiles, and the
-# two-call route (sigmoid, d > 104, wider tables, more leaves).
+# bit: the one-pass kernels (softmax, d <= 104, <= 256 leaves whose lr * V
+# table fits 64 KB, at each register-kernel width and ragged tiles; sigmoid with <=
+# 256 leaves), and the two-call route (softmax with d > 104 or wider tables, more
+# leaves).
 @pytest.mark.parametrize("loss,d,n_leaves,n", [
     ("softmax", 1, 1, 1000), ("softmax", 5, 64, 3 * 256 + 77), ("softmax", 17, 3, 2000), ("softmax", 33, 64, 2500),
     ("softmax", 64, 100, 1500), ("softmax", 100, 64, 2048 * 256 + 1000), ("softmax", 104, 78, 5000),

@@ -34,3 +34,18 @@ def test_wide_softmax_gradients(d, n):
     G1, H1, hr1, n1 = check_gradients("softmax", F_T, y)
     G2, H2, hr2, n2 = check_gradients("softmax", F_T, y)
     assert np.array_equal(G1, G2) and np.array_equal(H1, H2) and np.array_equal(hr1, hr2) and np.array_equal(n1, n2)
+
+
+# The two-pass softmax past 1024 columns: a full tile of 256 rows alone, with a
+# ragged one, and several, with one ragged last chunk of columns.
+@pytest.mark.parametrize("d,n", [(1025, 256), (1025, 257), (1041, 770)])
+def test_two_pass_softmax_gradients(d, n):
+    F_T, y = scores_and_targets(n, d, "softmax", seed=d + n, scale=2.0)
+    check_gradients("softmax", F_T, y)
+
+
+# A leading dimension of 2^24 takes narrower rows to the two-pass kernel too
+# (below it, the wide kernel): more tiles than the 1536 norm slots, so slots take two.
+def test_two_pass_softmax_by_leading_dimension():
+    F_T, y = scores_and_targets(1536 * 256 + 300, 106, "softmax", seed=5, scale=2.0)
+    check_gradients("softmax", F_T, y, ld_f=1 << 24)
