@@ -254,9 +254,10 @@ __global__ void __launch_bounds__(LEAF_THREADS) k_leaf_accum(LeafArgs a) {
     }
     const int64_t left = a.n - 1 - (int64_t)t * (LEAF_THREADS * SPT);  // the tile's last row
     // Past the last tile every lane loads this tile's first row, not used: one cache
-    // line per column instead of the tile once more (boosting iteration at 300,001
-    // rows x 203 outputs 920 -> 915 us).  A branch around the loads instead costs
-    // 10 us at 1M x 100 and 66 us in the iteration at 2M x 100.
+    // line per column instead of the tile once more (16 leaves, unit hessians: 1M x
+    // 30, where every block has one tile, 46.8 -> 33.9 us, 200,003 x 100 31.1 -> 24.5).
+    // A branch around the loads instead costs 10 us at 1M x 100 and 66 us in the
+    // iteration at 2M x 100.
     const int nt = t + 1 < t1 ? t + 1 : t;
     const uint32_t keep = t + 1 < t1 ? ~0u : 0u;
 #pragma unroll
@@ -273,7 +274,7 @@ __global__ void __launch_bounds__(LEAF_THREADS) k_leaf_accum(LeafArgs a) {
     // The next tile's adds (and its writes of wmax and sconv) start only after
     // its first barrier, which every thread reaches after finishing this loop.
     for (int cell = tid; cell < cells; cell += LEAF_THREADS) {
-      const int j = cell / NL;
+      const int j = J == 1 ? 0 : cell / NL;
       unsigned long long* cp = icell + ((cell + j) << rsh);  // one cell more per channel than acc
       long long q = 0;
       // (exact: the copies split one tile's sum; neighbouring lanes start at
@@ -283,7 +284,7 @@ __global__ void __launch_bounds__(LEAF_THREADS) k_leaf_accum(LeafArgs a) {
       for (int r = 0; r < (1 << rsh); ++r) cp[(r + lane) & ((1 << rsh) - 1)] = 0ull;
     }
   }
-  __syncthreads();
+  leaf_sync();
   for (int cell = tid; cell < cells; cell += LEAF_THREADS) {
     const int j = cell / NL, L = cell - j * NL;
     if (c0 + j < a.nch) a.part[((int64_t)L * a.nch + c0 + j) * gridDim.y + split] = acc[cell];
@@ -342,7 +343,9 @@ int64_t leaf_lds(int32_t n_leaves, int J, int rsh) {
 LeafPlan leaf_plan(int64_t n, int32_t nch, int32_t n_leaves, int jmax = LEAF_JMAX) {
   LeafPlan p{};
   p.J = jmax;
-  while (p.J > 1 && leaf_lds(n_leaves, p.J, 0) > LEAF_LDS_MAX) p.J >>= 1;
+  // no more channels than there are: one past the last costs its adds (one output with
+  // derived hessians, 512 leaves, 1M rows: 42.9 -> 31.0 us)
+  while (p.J / 2 >= nch || (p.J > 1 && leaf_lds(n_leaves, p.J, 0) > LEAF_LDS_MAX)) p.J >>= 1;
   p.nch = nch;
   p.n_chunks = (nch + p.J - 1) / p.J;
   p.n_tiles = (int)((n + LEAF_TILE - 1) / LEAF_TILE);

@@ -131,3 +131,30 @@ def test_leaf_values_from_loss(loss, n_leaves):
                                        hess_err=2.0 ** -22)
     assert ok, worst
     assert np.all(Vg[5] == 0)
+
+
+# One to three outputs: blocks narrower than the kernel's widest, with the loaded
+# and the derived hessians, 8- and 16-bit leaf ids.
+@pytest.mark.parametrize("d", [1, 2, 3])
+@pytest.mark.parametrize("n_leaves", [2, 256, 600])
+def test_leaf_values_few_outputs(d, n_leaves):
+    from oracle import boost as ob
+    from workloads import scores_and_targets
+    n = 2048 + 77
+    row_idx, leaf_off = grouping(n, n_leaves, seed=d + n_leaves)
+    F_T, Y = scores_and_targets(n, d, "sigmoid", seed=81 + d, scale=2.0)
+    G, Hd, hr, _ = ob.gradients("sigmoid", F_T.T, Y.T)
+    G_T, H_T = np.ascontiguousarray(G.T), np.ascontiguousarray(Hd.T)
+    check(G_T, row_idx, leaf_off, 1.0)
+    check(G_T, row_idx, leaf_off, 1.0, h=hr.astype(np.float32))
+    check(G_T, row_idx, leaf_off, 1.0, hess_T=H_T)
+    V = torch.full((n_leaves, d), float("nan"), dtype=torch.float64, device=gu.DEV)
+    ws = gu.workspace(gu.L.sb_workspace_bytes(gu.L.SB_CALL_LEAF_VALUES, n=n, d=d, n_nodes=n_leaves), gu.DEV)
+    gu.L.sb_leaf_values_from_loss(gu.L.LOSS["sigmoid"], gu.up(G_T), n, d, n, None, gu.up(Y), n, gu.up(row_idx),
+                                  gu.up(leaf_off), n_leaves, 1.0, V, d, ws, ws.numel())
+    gu.sync()
+    V_o = oracle.leaf_values(G, row_idx, leaf_off, 1.0, hess=Hd)
+    # (2^-22: as in test_leaf_values_from_loss)
+    ok, worst = gu.leaf_value_error_ok(V.cpu().numpy(), V_o, G, oracle.leaf_rows(row_idx, leaf_off), 1.0, hess=Hd,
+                                       hess_err=2.0 ** -22)
+    assert ok, worst
