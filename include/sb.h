@@ -265,7 +265,7 @@ int32_t sb_hist_exponents(const float* GH, int64_t n, int64_t ld_gh, int32_t k, 
  * H         out: [n_nodes][m][k+1][n_bins] fp64.
  * 1 <= k <= 23: more than 24 channels return SB_E_UNSUPPORTED.
  * The call first writes every row's quantised values into its workspace,
- * 16 * ceil((k+1)/6) bytes per row (one 16-byte word per group of six
+ * 16 * ceil((k+1)/6) bytes per row (one 16-byte word per group of up to six
  * channels), so the workspace grows with n:
  * sb_workspace_bytes(SB_CALL_BUILD_HISTOGRAMS, n, ...).
  */

@@ -32,6 +32,16 @@ __device__ inline double lane_strided_sum(const double* x, int count, int lane) 
   return s;
 }
 
+// Barrier that waits for this wave's LDS operations only: global loads and
+// stores stay in flight across it (a plain __syncthreads also waits for them).
+// 0xc07f is s_waitcnt lgkmcnt(0) in the gfx9 encoding.
+__device__ inline void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // A 32-bit value moved across lanes by a DPP control (row shift or row
 // broadcast); lanes the control does not write get `old`.
 template <int CTRL, int ROW_MASK>

@@ -5,8 +5,9 @@
 // k_grad: one thread per row, the rows of a block in one 256-row tile, tiles
 //   grid-strided.  The lanes of a wave take consecutive rows, so every load
 //   and store is one 256-byte run of a column of the column-major matrices.
-//   Softmax cross-entropy (rows of more than 1024 scores; narrower ones stay in
-//   registers, k_grad_softmax_regs and k_grad_softmax_wide): a first pass over the row's scores keeps a running
+//   Softmax cross-entropy (rows of more than 1024 scores, or leading dimensions
+//   of 2^24 and more; others stay in registers, k_grad_softmax_regs and
+//   k_grad_softmax_wide): a first pass over the row's scores keeps a running
 //   maximum and the sum of exp(a - max), rescaled chunk by chunk; the second
 //   pass re-reads the scores and writes g = p - onehot(y), h = p (1 - p).
 //   Sigmoid cross-entropy needs one pass: g = s - Y, h = s (1 - s).
@@ -25,11 +26,12 @@
 //   lr * V of a chunk of columns is staged in LDS; the leaf ids come from the
 //   leaf segments (k_leaf_ids, shared with the leaf values).
 // The update of one tree followed by the derivatives of the next (the two
-// consecutive steps of the boosting loop) can run as one pass for softmax
-// with d <= 104: k_grad_softmax_regs with UPD loads a row's scores, adds
-// lr * V of the row's leaf (all of lr * V staged in LDS), stores the new
-// scores and goes on from them, so F is read once instead of twice.  The
-// arithmetic is k_update's, so the result is bit-identical to the two calls.
+// consecutive steps of the boosting loop) can run as one pass, so that F is read
+// once instead of twice: for softmax with d <= 104 k_grad_softmax_regs with UPD
+// loads a row's scores, adds lr * V of the row's leaf (all of lr * V staged in
+// LDS), stores the new scores and goes on from them; for sigmoid
+// k_update_sigmoid does so by chunks of 16 columns.  The arithmetic is k_update's,
+// so the result is bit-identical to the two calls.
 #include <cmath>
 
 #include "sb_common.h"
@@ -39,21 +41,22 @@
 namespace sb {
 namespace {
 
-// Sum over each row of 16 lanes, in registers (no LDS traffic): shifts by 1,
-// 2, 4 and 8 lanes (lanes a shift does not write add 0), so the last lane of
-// each row ends with the row's sum, always added in the same order.
+// A double moved across lanes by a DPP control; lanes it does not write get 0.
 template <int CTRL>
-__device__ inline double dpp_row_shr(double x) {
+__device__ inline double dpp_f64(double x) {
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
 }
 
+// Sum over each row of 16 lanes, in registers (no LDS traffic): shifts by 1,
+// 2, 4 and 8 lanes (lanes a shift does not write add 0), so the last lane of
+// each row ends with the row's sum, always added in the same order.
 __device__ inline double row16_sum(double x) {
-  x += dpp_row_shr<0x111>(x);
-  x += dpp_row_shr<0x112>(x);
-  x += dpp_row_shr<0x114>(x);
-  x += dpp_row_shr<0x118>(x);
+  x += dpp_f64<0x111>(x);
+  x += dpp_f64<0x112>(x);
+  x += dpp_f64<0x114>(x);
+  x += dpp_f64<0x118>(x);
   return x;
 }
 
@@ -101,23 +104,12 @@ struct GradArgs {
   double lr;
 };
 
-// Barrier for the norm staging: waits for this wave's LDS operations only.
-// A plain __syncthreads also waits for every outstanding global access,
-// here the stores of G (and the hessians) of the chunk just written.
-// 0xc07f is s_waitcnt lgkmcnt(0) in the gfx9 encoding.
-__device__ inline void lds_sync() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // The squared norms of a tile's chunk of 16 columns from j0, staged in gbuf:
 // 16 threads per column add 16 rows each, and the column's sum goes to its
 // tile's slot.
 __device__ inline void add_norms(const GradArgs& a, float (*gbuf)[GRAD_THREADS], int64_t base, int d, int j0) {
   if (!a.npart) return;
-  lds_sync();
+  lds_barrier();
   // lanes c*16 .. c*16+15 share column c
   const int c = threadIdx.x >> 4, seg = threadIdx.x & 15;
   const float4* src = reinterpret_cast<const float4*>(&gbuf[c][seg * 16]);
@@ -136,7 +128,7 @@ __device__ inline void add_norms(const GradArgs& a, float (*gbuf)[GRAD_THREADS],
     double* pp = a.npart + (int64_t)(j0 + c) * a.n_parts + tile % a.n_parts;
     *pp = tile < a.n_parts ? acc : *pp + acc;  // the slot's first tile writes it
   }
-  lds_sync();
+  lds_barrier();
 }
 
 // One tile of k_grad (the loss, whether the tile is full and whether the
@@ -456,12 +448,6 @@ __global__ void __launch_bounds__(GRAD_THREADS) k_grad_softmax_regs(GradArgs a) 
 // so lane l ends with column l mod 32's sum over its rows, in a fixed order, and
 // adds it to its own fp64 total over the block's tiles.  Block b's totals are
 // partial b.
-template <int CTRL>
-__device__ inline double dpp_double(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
 // v[0..N): the lane keeps the half of the columns that its bit names, adds the
 // partner's values of them and passes the other half on.
 template <int CTRL, int N>
@@ -470,7 +456,7 @@ __device__ inline void exchange_half(double (&v)[16], bool upper) {
   for (int c = 0; c < N / 2; ++c) {
     const double keep = upper ? v[c + N / 2] : v[c];
     const double send = upper ? v[c] : v[c + N / 2];
-    v[c] = keep + dpp_double<CTRL>(send);
+    v[c] = keep + dpp_f64<CTRL>(send);
   }
 }
 __device__ inline void swap_rows(float& x, float& y) {  // x's odd rows of 16 lanes <-> y's even rows
@@ -536,7 +522,7 @@ __device__ __forceinline__ void softmax_wide_wave(const GradArgs& a, float (*sre
     for (int i = 4; i < WIDE_C; ++i) m4[i & 3] = fmaxf(m4[i & 3], x[i]);
     float m = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
     sred[0][w][lane] = m;
-    lds_sync();
+    lds_barrier();
     for (int u = 0; u < nw; ++u)
 #pragma unroll
       for (int h = 0; h < PARTS; ++h) m = fmaxf(m, sred[0][u][ROWS * h + rl]);
@@ -548,7 +534,7 @@ __device__ __forceinline__ void softmax_wide_wave(const GradArgs& a, float (*sre
       s += (FULLC || c0 + i <= last) ? x[i] : 0.0f;
     }
     sred[1][w][lane] = s;
-    lds_sync();
+    lds_barrier();
     s = 0.0f;
     for (int u = 0; u < nw; ++u)
 #pragma unroll
@@ -611,7 +597,7 @@ __device__ __forceinline__ void softmax_wide_wave(const GradArgs& a, float (*sre
     total += v[0];
     if (a.h_row) {
       sred[2][w][lane] = hsum;
-      lds_sync();
+      lds_barrier();
       if (w == 0 && hb == 0 && ok) {
         float hs = 0.0f;
         for (int u = 0; u < nw; ++u)

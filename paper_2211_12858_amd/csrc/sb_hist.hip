@@ -260,16 +260,6 @@ __device__ inline void fold_cells(const uint64_t* lds64, int64_t* tot) {
   asm volatile("" ::: "memory");
 }
 
-// Barrier for the window folds: waits for this wave's LDS operations only, so
-// global prefetches stay in flight across it (a plain __syncthreads also
-// drains them).  0xc07f is s_waitcnt lgkmcnt(0) in the gfx9 encoding.
-__device__ inline void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // A lane's position in a step: `raw` is the row index as loaded (not yet
 // clamped, so that issuing the load never waits for it) and `on` says whether
 // the position exists.

@@ -27,7 +27,8 @@ static_assert((int64_t)WINDOW_ROWS * (1ll << QBITS) < (1ll << 31), "fixed-point 
 constexpr int QFIELD_BITS = 21;
 constexpr int QROW_MAX_C = 6;
 // More channels take several such words per row, one per channel group of
-// six; each group gets workgroups of its own (up to ROT_MAX_C channels).
+// four or six (see HistPlan); each group gets workgroups of its own (up to
+// ROT_MAX_C channels).
 constexpr int ROT_MAX_C = 24;
 static_assert(QBITS + 2 <= QFIELD_BITS, "a quantised value of magnitude <= 2^QBITS and its sign must fit a field");
 

@@ -157,15 +157,6 @@ __device__ inline float wave_max_nonneg(float x) {
   return x;
 }
 
-// Barrier that waits for LDS operations only: the next tile's loads stay in
-// flight across it.  0xc07f is s_waitcnt lgkmcnt(0) in the gfx9 encoding.
-__device__ inline void leaf_sync() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // One block's tiles.  Per tile: block-wide maximum per channel, quantisation,
 // integer adds into the LDS cells, then the exact fp64 conversion into the
 // accumulators.  As a row's values are added, its registers take the row's
@@ -229,7 +220,7 @@ __global__ void __launch_bounds__(LEAF_THREADS) k_leaf_accum(LeafArgs a) {
   }
   for (int cell = tid; cell < icells; cell += LEAF_THREADS) icell[cell] = 0ull;
   for (int cell = tid; cell < cells; cell += LEAF_THREADS) acc[cell] = 0.0;
-  leaf_sync();
+  lds_barrier();
 
   for (int t = t0; t < t1; ++t) {
 #pragma unroll
@@ -240,7 +231,7 @@ __global__ void __launch_bounds__(LEAF_THREADS) k_leaf_accum(LeafArgs a) {
       mx = wave_max_nonneg(mx);
       if (lane == 63) wmax[wave][j] = mx;
     }
-    leaf_sync();
+    lds_barrier();
     double sc[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -270,7 +261,7 @@ __global__ void __launch_bounds__(LEAF_THREADS) k_leaf_accum(LeafArgs a) {
         atomicAdd(cell + j * chan, (unsigned long long)rint_to_ll(leaf_value<J, SPT, DER>(x, s, j, c0), sc[j]));
       load_row(x, nt, s, keep);
     }
-    leaf_sync();
+    lds_barrier();
     // The next tile's adds (and its writes of wmax and sconv) start only after
     // its first barrier, which every thread reaches after finishing this loop.
     for (int cell = tid; cell < cells; cell += LEAF_THREADS) {
@@ -284,7 +275,7 @@ __global__ void __launch_bounds__(LEAF_THREADS) k_leaf_accum(LeafArgs a) {
       for (int r = 0; r < (1 << rsh); ++r) cp[(r + lane) & ((1 << rsh) - 1)] = 0ull;
     }
   }
-  leaf_sync();
+  lds_barrier();
   for (int cell = tid; cell < cells; cell += LEAF_THREADS) {
     const int j = cell / NL, L = cell - j * NL;
     if (c0 + j < a.nch) a.part[((int64_t)L * a.nch + c0 + j) * gridDim.y + split] = acc[cell];
