@@ -684,14 +684,20 @@ __global__ void __launch_bounds__(PT_THREADS) k_part_scan_scatter(PartArgs a) {
 // Small levels (up to PT_ONE_ROWS rows and PT_ONE_NODES nodes) in one launch
 // of one 1024-thread block: what k_part_flags_pick and k_part_scan_scatter do,
 // with the ballots, their prefix and the left-count bases in LDS.  Two
-// dependent launches cost such a level more than the work (10,000 rows: 10.7 us,
-// 9.0 us here, trees 110.7 -> 105.0 us; at 20,000 rows one block takes 15 us
-// against 12).  Thread
+// dependent launches take 10.5 us whatever a small level's size; one block takes
+// 7.8 us up to 4096 rows, and at 10,240 rows 7.8 us with one node, 10.7 with 16
+// and 12.5 with 32, whose rows lie in more runs.  So the per-step call takes it up to
+// PT_ONE_WORK rows x nodes.  Inside a tree the nodes' splits are picked in the same
+// launch, which two launches do once per block: there 32 nodes gain up to the last
+// row (trees of depth 6 on 10,000 x 50 261 -> 257 us by it, x 200 222 -> 216, x 2000
+// 452 -> 436).  Past 10,240 rows one block gains less than 2% of a tree, from 16,000 it
+// loses.  Thread
 // t takes the positions t + 1024 it, it < ITERS, so ballot 16 it + wave is the
 // ballot of 64 consecutive positions, in position order.
 constexpr int PT_ONE_THREADS = 1024;
 constexpr int64_t PT_ONE_ROWS = 10 * PT_ONE_THREADS;
 constexpr int PT_ONE_NODES = 32;
+constexpr int64_t PT_ONE_WORK = 16 * PT_ONE_ROWS;
 
 template <bool PICK, int ITERS>
 __global__ void __launch_bounds__(PT_ONE_THREADS) k_part_one(PartArgs a) {
@@ -882,7 +888,7 @@ int32_t launch_partition(const uint8_t* bins_cm, int64_t n, int32_t m, int64_t l
       a.out_b = const_cast<int32_t*>(best_b);
       a.out_s = best_s;
     }
-    if (n <= PT_ONE_ROWS && n_nodes <= PT_ONE_NODES) {
+    if (n <= PT_ONE_ROWS && n_nodes <= PT_ONE_NODES && (feat_s || n * n_nodes <= PT_ONE_WORK)) {
 #define SB_ONE(I)                                                                                        \
   do {                                                                                                   \
     if (feat_s) hipLaunchKernelGGL((k_part_one<true, I>), dim3(1), dim3(PT_ONE_THREADS), 0, st, a);      \
