@@ -59,7 +59,10 @@ static int row_groups(int uf) {
 // takes 0.85 us, a full slice's 2 us), more adds than that their share.  With
 // f alone as its cost, 200,000 rows x 50 features gave the 2-feature slice 13
 // of 256 workgroups, and the root took 32 us instead of 17; with more than 6,
-// the root of 1M x 99 x 21 channels 284 instead of 255 us.
+// the root of 1M x 99 x 21 channels 284 instead of 255 us.  Trees of one level over 17
+// to 104 features, 4 and 8 against 6: at 2M rows 4 takes up to 31% longer (66
+// features, 3 channels), 8 up to 24% less at 3 channels (100 features, 203 -> 155
+// us), 1 to 3% longer at 6 and 11.
 static double thin_row_cost(int f) { return fmax(6.0, 2.0 + 0.875 * f); }
 
 HistPlan hist_plan(int32_t m, int32_t n_bins, int32_t k, int32_t n_build, bool thin_ok) {
